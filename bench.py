@@ -87,7 +87,7 @@ def profile_traffic_for(args, options):
 
 
 # The sources whose code the relaxation kernel's traffic depends on.
-KERNEL_SOURCES = ("relax.hpp", "relax_grid.hip", "kernels.hip", "device.hpp")
+KERNEL_SOURCES = ("relax.hpp", "table_rounds.hpp", "relax_grid.hip", "kernels.hip", "device.hpp")
 
 
 def kernel_source_digest():

@@ -33,6 +33,8 @@ def _flags():
     return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
             # packed fp32 instructions are kept out of every kernel
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            # atomics stay as written: the kernels aggregate over a wave by hand where that pays
+            "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
             "-Wall", "-Wno-unused-command-line-argument", "-I", INCLUDE, "-I", CSRC]
 
 

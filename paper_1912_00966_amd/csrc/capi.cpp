@@ -522,6 +522,7 @@ eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan 
   } else if (o.table_cap > 0) {
     H = o.table_cap;
   }
+  if (max_v > kMaxTableStops) H = 0;
   // a frontier never holds more items than there are stops (or table slots)
   const int items = std::max(64, (std::max(max_v, H) + 63) / 64 * 64);
   fcap = std::min(fcap, items);

@@ -108,6 +108,9 @@ constexpr int queries_per_cu(int block) {
 // LDS a relaxation work-group holds besides the dynamic part the plan sizes
 // (its counters and the start bits of the type windows).
 constexpr size_t kStaticLds = 2048;
+// Graphs of more stops run without the on-chip table (a slot holds 29 bits of
+// a stop's number).
+constexpr int32_t kMaxTableStops = 0x1fffffff;
 constexpr int kMaxBuckets = 32;
 constexpr int kCounterWords = 4 + kMaxBuckets;
 

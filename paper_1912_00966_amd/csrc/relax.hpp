@@ -61,7 +61,8 @@ constexpr int kClaim = 4;  // frontier entries a wave claims at a time (rounds o
 // A round's connection types, numbered in list order, are cut into windows of
 // 64; a wave relaxes whole windows.  Rounds of up to kWin windows take this
 // path; larger ones fall back to claims of kClaim entries.
-constexpr int kWin = 128;
+constexpr int kTabWin = 80;         // table_rounds: windows of the round's list and of the next one's
+constexpr int kWin = 2 * kTabWin;   // run_rounds: one list's
 // Chunks of the slab fill a lane issues per step a wave waits for others.
 constexpr int32_t kFillPerStep = 8;
 
@@ -96,7 +97,19 @@ struct GraphG {
   float inv_cw;
 };
 
-__device__ __forceinline__ GraphG graph_g(const GraphDev &g) {
+// The launch arguments' device arrays that no kernel writes, read through the
+// scalar cache: a work-group's descriptor and query record stay in scalar
+// registers, and no vector load of theirs is in flight when the rounds begin.
+#if defined(__HIP_DEVICE_COMPILE__)
+template <class T>
+using cp = __attribute__((address_space(4))) const T *;
+#else
+template <class T>
+using cp = const T *;
+#endif
+
+template <class D>
+__device__ __forceinline__ GraphG graph_g(const D &g) {
   GraphG o;
   o.vt = (gp<const int2>)g.vt;
   o.ty = (gp<const int4>)g.ty;
@@ -777,6 +790,18 @@ __device__ __forceinline__ void relax(const GraphG &G, const Store &S, int64_t j
   relax_batch<KIND, 1>(G, S, &j, &b, &n, &x, &ok, P, c);
 }
 
+// What the waves add up in one round of table_rounds.
+constexpr uint32_t kTableFull = 0x80000000u;
+struct alignas(16) PushCtr {
+  unsigned long long cx;  // low half entries pushed, high half (near list) their types
+  int32_t min;            // smallest arrival among them
+  uint32_t extra;         // near: stops new in the table, kTableFull: one found no slot;
+                          // far: best arrival at the target (goal-directed queries)
+};
+struct RoundCtr {
+  PushCtr near, far;
+};
+
 struct Shared {
   int32_t q, cnt, count, over, reached;
   int32_t bound;                // goal-directed queries: best arrival at the target so far
@@ -787,11 +812,14 @@ struct Shared {
   unsigned long long cx[3];     // round r: low half entries pushed to the next list
   unsigned long long xt[3];     // round r (per sweep chunk): low half X entries, high half their types
   unsigned long long acc[5];
+  unsigned long long t_start;   // device clock when the query began
   // windows of 64 types: bit i of wstart[w] is set if an X entry's types start
   // at type 64 w + i; wentry[w] is the X entry holding type 64 w.  A wave
   // clears the bits of each window it relaxes, so they are zero between rounds.
-  unsigned long long wstart[kWin];
-  int32_t wentry[kWin];
+  // (table_rounds: two halves of kTabWin windows, used in turn; see list_near.)
+  unsigned long long wstart[2 * (kTabWin + 1)];
+  uint16_t wentry[kWin];
+  RoundCtr rc[3];
   // the infinity fill of the result slab still to issue: 16-byte chunks
   // [fill_next, fill_n4) of fill_p (table queries; see fill_idle)
   int4 *fill_p;
@@ -931,7 +959,7 @@ __device__ __forceinline__ void expand_list(const GraphG &G, const Store &S, con
           X[slot] = make_int4(beg, cnt, x, toff);
           if ((toff >> 6) < kWin) atomicOr(&sh.wstart[toff >> 6], 1ull << (toff & 63));
           // the windows whose first type is one of this entry's
-          for (int32_t w = (toff + 63) >> 6; w < kWin && (w << 6) < toff + cnt; ++w) sh.wentry[w] = slot;
+          for (int32_t w = (toff + 63) >> 6; w < kWin && (w << 6) < toff + cnt; ++w) sh.wentry[w] = (uint16_t)slot;
         }
       }
     }
@@ -1073,6 +1101,8 @@ __device__ __forceinline__ void expand_list(const GraphG &G, const Store &S, con
 struct QState {
   int32_t rounds = 0, sweeps = 0, maxf = 1, status = EAT_OK;
 };
+
+#include "table_rounds.hpp"
 
 // Relaxation rounds until no arrival improves (the iteration of Algorithms 4
 // and 5, with the activity flags of Section III-B).  On entry the first item
@@ -1244,6 +1274,7 @@ __device__ __forceinline__ void slab_query(const RunArgs &a, const GraphG &G, gp
   const int32_t VW = (V + 31) >> 5;
   const FList l0{l, l + F, l + 2 * F}, l1{l + 3 * F, l + 4 * F, l + 5 * F};
   for (int32_t i = tid; i < VW; i += B) bits_st(bits, i, 0u);
+  for (int32_t i = tid; i < 2 * (kTabWin + 1); i += B) sh.wstart[i] = 0ull;  // a table that overflowed left marks
   if (tid == 0) {
     sh.over = 0;
     sh.fill_n4 = 0;  // the fill is complete: the slab now holds the arrivals
@@ -1274,71 +1305,93 @@ __device__ __forceinline__ void slab_query(const RunArgs &a, const GraphG &G, gp
   if (mine) atomicAdd(&sh.reached, mine);
 }
 
+__device__ __forceinline__ QueryDev query_c(cp<QueryDev> p) { return QueryDev{p->graph, p->s, p->ts, p->index, p->arr}; }
+
+// The launch arguments, read again: what a phase of the kernel needs of them is
+// loaded (scalar cache) when the phase begins and not kept in scalar registers
+// over the others, which need all there are for the rounds.
+__device__ __forceinline__ RunArgs args_again() {
+  RunArgs a;
+#if defined(__HIP_DEVICE_COMPILE__)
+  cp<RunArgs> p = (cp<RunArgs>)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  __builtin_memcpy(&a, (const RunArgs *)p, sizeof(a));
+#endif
+  return a;
+}
+__device__ __forceinline__ QueryDev query_again(const RunArgs &a, const Shared &sh) {
+  return a.queries ? query_c((cp<QueryDev>)a.queries + uniform(sh.q)) : a.single;
+}
+__device__ __forceinline__ GraphG graph_again(const RunArgs &a, const QueryDev &Q) {
+  return graph_g(*((cp<GraphDev>)a.graphs + (a.queries ? Q.graph : 0)));
+}
+__device__ __forceinline__ int32_t round_limit(const RunArgs &a, int32_t V) {
+  return a.max_rounds > 0 ? a.max_rounds : (a.window > 0 ? 8 * V + 64 : V + 2);
+}
+
 // 768-thread work-groups share a CU two at a time, 384-thread ones four and
 // 256-thread ones six at a time: 24 waves, 6 per SIMD, which needs at most
 // 80 VGPRs: asked of the compiler here.
 template <int TPV, int KIND, int U, int B, bool GOAL>
 __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
-    B == kBlockMid || B == kBlockQuarter || B == kBlockSixth ? 6 : 1))) void k_relax(RunArgs a) {
+    B == kBlockMid || B == kBlockQuarter || B == kBlockSixth ? 6 : 1))) void k_relax(RunArgs) {
   extern __shared__ __align__(16) uint32_t lds[];
   __shared__ Shared sh;
 
   const int tid = threadIdx.x;
-  const bool batch = a.queries != nullptr;
-  const bool topo = a.mode == EAT_MODE_TOPOLOGY;
-  const int32_t F = a.fcap;
+  constexpr bool kTagged = TPV == 0 && U == 1;  // the rounds of table_rounds.hpp
+  // LDS: X (F x 16 bytes) | table slots or slab bits | two lists (item, beg, cnt) x F;
+  // table_rounds: near list | table | near list | two far lists (F / 2 x 8 bytes each)
+  const XList X = reinterpret_cast<int4 *>(lds);
 
   for (int iter = 0;; ++iter) {
-    if (tid == 0) {
-      int32_t q = a.nq;
-      if (batch) {
-        const int32_t nb = a.n_buckets;
-        int32_t b = (int32_t)(blockIdx.x % (uint32_t)nb);
-        for (int32_t k = 0; k < nb; ++k, b = (b + 1 == nb) ? 0 : b + 1) {
-          const int32_t lo = a.buckets[b], cnt = a.buckets[b + 1] - lo;
-          int32_t *cursor = a.work + 4 + b;
-          if (__hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= cnt) continue;
-          const int32_t i = __hip_atomic_fetch_add(cursor, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (i < cnt) {
-            q = lo + i;
-            break;
+    {
+      const RunArgs a = args_again();
+      const bool batch = a.queries != nullptr;
+      if (tid == 0) {
+        int32_t q = a.nq;
+        if (batch) {
+          const int32_t nb = a.n_buckets;
+          int32_t b = (int32_t)(blockIdx.x % (uint32_t)nb);
+          for (int32_t k = 0; k < nb; ++k, b = (b + 1 == nb) ? 0 : b + 1) {
+            const int32_t lo = a.buckets[b], cnt = a.buckets[b + 1] - lo;
+            int32_t *cursor = a.work + 4 + b;
+            if (__hip_atomic_load(cursor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= cnt) continue;
+            const int32_t i = __hip_atomic_fetch_add(cursor, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (i < cnt) {
+              q = lo + i;
+              break;
+            }
+          }
+        } else if (iter == 0) {
+          q = 0;
+        }
+        sh.q = q;
+      }
+      if (tid < 5) sh.acc[tid] = 0ull;
+      if (tid < 2 * (kTabWin + 1)) sh.wstart[tid] = 0ull;
+      if (tid == 0) {
+        sh.count = 0;
+        sh.over = 0;
+        sh.reached = 0;
+      }
+      __syncthreads();
+      if (uniform(sh.q) >= a.nq) {
+        // The last work-group to leave re-arms the shared counters for the next
+        // launch of the same batch, so a run is a single kernel launch.
+        if (batch && tid == 0) {
+          const int32_t left = __hip_atomic_fetch_add(a.work, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+          if (left == (int32_t)gridDim.x - 1) {
+            const int32_t failed = __hip_atomic_exchange(a.work + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.work + 2, failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int32_t b = 0; b < a.n_buckets; ++b)
+              __hip_atomic_store(a.work + 4 + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.work, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
         }
-      } else if (iter == 0) {
-        q = 0;
+        break;
       }
-      sh.q = q;
     }
-    if (tid < 5) sh.acc[tid] = 0ull;
-    if (tid < kWin) sh.wstart[tid] = 0ull;
-    if (tid == 0) {
-      sh.count = 0;
-      sh.over = 0;
-      sh.reached = 0;
-    }
-    __syncthreads();
-    const int32_t q = uniform(sh.q);
-    if (q >= a.nq) {
-      // The last work-group to leave re-arms the shared counters for the next
-      // launch of the same batch, so a run is a single kernel launch.
-      if (batch && tid == 0) {
-        const int32_t left = __hip_atomic_fetch_add(a.work, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (left == (int32_t)gridDim.x - 1) {
-          const int32_t failed = __hip_atomic_exchange(a.work + 1, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(a.work + 2, failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          for (int32_t b = 0; b < a.n_buckets; ++b)
-            __hip_atomic_store(a.work + 4 + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(a.work, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-      }
-      break;
-    }
-    const uint64_t t_start = wall_clock64();
-    const QueryDev Q = batch ? a.queries[q] : a.single;
-    const GraphG G = graph_g(a.graphs[batch ? Q.graph : 0]);
-    const int32_t V = G.n_vertices;
-    gp<int32_t> arr = (gp<int32_t>)Q.arr;
-    const int32_t max_rounds = a.max_rounds > 0 ? a.max_rounds : (a.window > 0 ? 8 * V + 64 : V + 2);
     QState qs;
     Ctr c;
 
@@ -1347,88 +1400,133 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
     // the graph's lines that the relaxation reads).  A table query's fill is
     // issued while its rounds run (fill_issue), the rest after them; a slab
     // query needs it first.
-    const bool aligned = (reinterpret_cast<uintptr_t>(arr) & 15u) == 0;
-    if (aligned && a.table_cap > 0) {
-      for (int32_t i = ((V >> 2) << 2) + tid; i < V; i += B) arr[i] = INF;
-      if (tid == 0) {
-        sh.fill_p = reinterpret_cast<int4 *>(arr);
-        sh.fill_n4 = V >> 2;
-        sh.fill_next = 0;
-      }
-    } else {
-      if (aligned) {
-        gp<v4i> a4 = (gp<v4i>)arr;
-        const int32_t n4 = V >> 2;
-        const v4i inf4 = {INF, INF, INF, INF};
-        for (int32_t i = tid; i < n4; i += B) __builtin_nontemporal_store(inf4, a4 + i);
-        for (int32_t i = (n4 << 2) + tid; i < V; i += B) arr[i] = INF;
+    {
+      const RunArgs a = args_again();
+      const QueryDev Q = query_again(a, sh);
+      const int32_t V = ((cp<GraphDev>)a.graphs + (a.queries ? Q.graph : 0))->n_vertices;
+      gp<int32_t> arr = (gp<int32_t>)Q.arr;
+      if (tid == 0) sh.t_start = wall_clock64();
+      const bool aligned = (reinterpret_cast<uintptr_t>(Q.arr) & 15u) == 0;
+      if (aligned && a.table_cap > 0) {
+        for (int32_t i = ((V >> 2) << 2) + tid; i < V; i += B) arr[i] = INF;
+        if (tid == 0) {
+          sh.fill_p = reinterpret_cast<int4 *>(Q.arr);
+          sh.fill_n4 = V >> 2;
+          sh.fill_next = 0;
+        }
       } else {
-        for (int32_t i = tid; i < V; i += B) arr[i] = INF;
-      }
-      if (tid == 0) {
-        sh.fill_p = nullptr;
-        sh.fill_n4 = 0;
-        sh.fill_next = 0;
+        if (aligned) {
+          gp<v4i> a4 = (gp<v4i>)arr;
+          const int32_t n4 = V >> 2;
+          const v4i inf4 = {INF, INF, INF, INF};
+          for (int32_t i = tid; i < n4; i += B) __builtin_nontemporal_store(inf4, a4 + i);
+          for (int32_t i = (n4 << 2) + tid; i < V; i += B) arr[i] = INF;
+        } else {
+          for (int32_t i = tid; i < V; i += B) arr[i] = INF;
+        }
+        if (tid == 0) {
+          sh.fill_p = nullptr;
+          sh.fill_n4 = 0;
+          sh.fill_next = 0;
+        }
       }
     }
 
-    bool done = false;
-    // LDS: X (F x 16 bytes) | table slots or slab bits | two lists (item, beg, cnt) x F
-    const XList X = reinterpret_cast<int4 *>(lds);
-    uint32_t *const store = lds + 4 * F;
-    if (a.table_cap > 0) {
-      // ---- arrivals in the on-chip table ----------------------------------------
+    bool ok = false;
+    {
+      const RunArgs a = args_again();
       const int32_t H = a.table_cap;
-      TableStore T;
-      T.kv = reinterpret_cast<unsigned long long *>(store);
-      T.count = &sh.count;
-      T.over = &sh.over;
-      T.mask = (uint32_t)H - 1u;
-      T.shift = 32 - a.table_bits;
-      T.limit = H - H / 4;
-      int32_t *l = reinterpret_cast<int32_t *>(T.kv + H);
-      const FList l0{l, l + F, l + 2 * F}, l1{l + 3 * F, l + 4 * F, l + 5 * F};
-      for (int32_t i = tid; i < H; i += B) T.kv[i] = EMPTY_SLOT;
-      __syncthreads();
-      if (tid == 0) {
-        const uint32_t p = T.home(Q.s);  // empty table: the home slot is free
-        T.kv[p] = ((unsigned long long)(uint32_t)Q.ts << 32) | (uint32_t)Q.s;  // active
-        sh.count = 1;
-        if constexpr (GOAL) sh.bound = batch_target(a, Q) == Q.s ? Q.ts : INF;
-        l0.item[0] = (int32_t)p;
-        l0.cnt[0] = -1;
-      }
-      __syncthreads();
-      bool ok;
-      if constexpr (GOAL) {
-        GoalStore<TableStore> GS;
-        static_cast<TableStore &>(GS) = T;
-        GS.bound = &sh.bound;
-        GS.target = batch_target(a, Q);
-        ok = run_rounds<TPV, KIND, U, B>(a, G, GS, H, l0, l1, X, topo, max_rounds, Q.ts, sh, qs, c);
-      } else {
-        ok = run_rounds<TPV, KIND, U, B>(a, G, T, H, l0, l1, X, topo, max_rounds, Q.ts, sh, qs, c);
-      }
-      fill_rest<B>(sh);  // before the final values, or before slab mode after an overflow
-      if (ok) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the infinity fill has landed
-        __syncthreads();
-        for (int32_t p = tid; p < H; p += B) {
-          const unsigned long long e = T.kv[p];
-          const uint32_t key = (uint32_t)e;
-          // nontemporal like the fill: the reached stops' lines are not read again
-          if (key != NO_KEY) __builtin_nontemporal_store((int32_t)(e >> 32), arr + (key & ~IDLE));
+      if (H > 0) {
+        // ---- arrivals in the on-chip table ----------------------------------------
+        const QueryDev Q = query_again(a, sh);
+        const GraphG G = graph_again(a, Q);
+        const int32_t F = a.fcap;
+        const bool topo = a.mode == EAT_MODE_TOPOLOGY;
+        unsigned long long *const kv = reinterpret_cast<unsigned long long *>(lds + 4 * F);
+        if constexpr (kTagged) {
+          TagTable T;
+          T.kv = kv;
+          T.mask = (uint32_t)H - 1u;
+          T.shift = 32 - a.table_bits;
+          const int2 rg = G.vt[Q.s];
+          int4 *const near0 = X, *const near1 = reinterpret_cast<int4 *>(kv + H);
+          int2 *const far0 = reinterpret_cast<int2 *>(near1 + F), *const far1 = far0 + (F >> 1);
+          ulonglong2 *const kv2 = reinterpret_cast<ulonglong2 *>(kv);
+          for (int32_t i = tid; i < (H >> 1); i += B) kv2[i] = ulonglong2{EMPTY_SLOT, EMPTY_SLOT};
+          if (tid < kTabWin) sh.wentry[tid] = 0;  // the source's types are the first list's only ones
+          wait_vector_memory<0>();
+          __syncthreads();
+          int32_t target = -1, bound = INF, reached = 0;
+          if constexpr (GOAL) {
+            target = batch_target(a, Q);
+            if (target == Q.s) bound = Q.ts;
+          }
+          if (tid == 0) {
+            const uint32_t p = T.home(Q.s);  // empty table: the home slot is free
+            kv[p] = ((unsigned long long)(uint32_t)Q.ts << 32) | NEAR_A | (uint32_t)Q.s;
+            near0[0] = make_int4(rg.x, rg.y, 0, (int32_t)p);
+            sh.rc[0] = RoundCtr{{0ull, INF, 0u}, {0ull, INF, (uint32_t)INF}};
+            sh.rc[2] = RoundCtr{{rg.y > 0 ? 1ull | ((unsigned long long)(uint32_t)rg.y << 32) : 0ull, Q.ts, 0u},
+                                {0ull, INF, (uint32_t)INF}};
+          }
+          ok = table_rounds<KIND, B, GOAL>(a, G, T, H, near0, near1, far0, far1, F >> 1, topo,
+                                           round_limit(a, G.n_vertices), bound, target, sh, qs, reached, c);
+          if (tid == 0) sh.count = reached;
+        } else {
+          TableStore T;
+          T.kv = kv;
+          T.count = &sh.count;
+          T.over = &sh.over;
+          T.mask = (uint32_t)H - 1u;
+          T.shift = 32 - a.table_bits;
+          T.limit = H - H / 4;
+          int32_t *l = reinterpret_cast<int32_t *>(kv + H);
+          const FList l0{l, l + F, l + 2 * F}, l1{l + 3 * F, l + 4 * F, l + 5 * F};
+          for (int32_t i = tid; i < H; i += B) kv[i] = EMPTY_SLOT;
+          __syncthreads();
+          if (tid == 0) {
+            const uint32_t p = T.home(Q.s);  // empty table: the home slot is free
+            kv[p] = ((unsigned long long)(uint32_t)Q.ts << 32) | (uint32_t)Q.s;  // active
+            sh.count = 1;
+            l0.item[0] = (int32_t)p;
+            l0.cnt[0] = -1;
+          }
+          __syncthreads();
+          ok = run_rounds<TPV, KIND, U, B>(a, G, T, H, l0, l1, X, topo, round_limit(a, G.n_vertices), Q.ts, sh, qs, c);
         }
-        if (tid == 0) sh.reached = sh.count;
-        done = true;
+        fill_rest<B>(sh);  // before the final values, or before slab mode after an overflow
       }
     }
-    if (!done) {
+    const bool done = ok;
+    if (done) {
+      const RunArgs a = args_again();
+      gp<int32_t> arr = (gp<int32_t>)query_again(a, sh).arr;
+      const int32_t H = a.table_cap;
+      const unsigned long long *const kv = reinterpret_cast<const unsigned long long *>(lds + 4 * a.fcap);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the infinity fill has landed
+      __syncthreads();
+      constexpr uint32_t kStop = kTagged ? STOP_MASK : ~IDLE;
+      for (int32_t p = tid; p < H; p += B) {
+        const unsigned long long e = kv[p];
+        const uint32_t key = (uint32_t)e;
+        // nontemporal like the fill: the reached stops' lines are not read again
+        if (key != NO_KEY) __builtin_nontemporal_store((int32_t)(e >> 32), arr + (key & kStop));
+      }
+      if (tid == 0) sh.reached = sh.count;
+    } else {
       // ---- arrivals in the result slab (no table, or the table overflowed) ----------
       // An overflowed table attempt never wrote the slab: it holds infinity once
       // the fill issued above has landed (slab_query waits for it).
       // The bitmap in HBM (it does not fit the LDS) is compiled into the
       // 1024-thread kernels only; the host runs such graphs with those.
+      const RunArgs a = args_again();
+      const QueryDev Q = query_again(a, sh);
+      const GraphG G = graph_again(a, Q);
+      const int32_t V = G.n_vertices;
+      gp<int32_t> arr = (gp<int32_t>)Q.arr;
+      const bool topo = a.mode == EAT_MODE_TOPOLOGY;
+      const int32_t max_rounds = round_limit(a, V);
+      uint32_t *const store = lds + 4 * a.fcap;
       bool in_hbm = false;
       if constexpr (B == kBlock) {
         if (a.bits_global) {  // this work-group's region of HBM
@@ -1444,6 +1542,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
     }
 
     // ---- per-query statistics --------------------------------------------------
+    const RunArgs a = args_again();
     if (a.stats || (qs.status != EAT_OK && a.n_failed)) {
       // wave sums first, then one LDS atomic per wave and counter
       uint32_t v5[5] = {c.act, c.tev, c.hdr, c.pool, c.imp};
@@ -1459,7 +1558,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
       __syncthreads();
       if (tid == 0) {
         if (a.stats) {
-          eat_query_stats *st = a.stats + Q.index;
+          eat_query_stats *st = a.stats + query_again(a, sh).index;
           st->status = qs.status;
           st->rounds = qs.rounds;
           st->sweep_rounds = qs.sweeps;
@@ -1471,7 +1570,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
           st->header_loads = (int64_t)sh.acc[2];
           st->pool_loads = (int64_t)sh.acc[3];
           st->improvements = (int64_t)sh.acc[4];
-          st->elapsed_ns = (int64_t)((wall_clock64() - t_start) * (uint64_t)a.ns_per_tick >> 10);
+          st->elapsed_ns = (int64_t)((wall_clock64() - sh.t_start) * (uint64_t)a.ns_per_tick >> 10);
         }
         if (qs.status != EAT_OK && a.n_failed)
           __hip_atomic_fetch_add(a.n_failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1482,7 +1581,8 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
       // scope before the query's completion word does
       __threadfence_system();
       __syncthreads();
-      if (tid == 0) __hip_atomic_store(a.done + Q.index, a.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (tid == 0)
+        __hip_atomic_store(a.done + query_again(a, sh).index, a.epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     __syncthreads();
   }

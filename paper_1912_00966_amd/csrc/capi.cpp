@@ -508,7 +508,7 @@ eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan 
   // default list capacity: the largest that still leaves room for a
   // 16,384-slot table (1024 threads) or an 8,192-slot one (512, 768 threads);
   // with four or six queries per CU, a 4,096- or 2,048-slot table
-  int fcap = o.frontier_cap ? o.frontier_cap : (qpc >= 4 ? 128 : small ? 256 : 704);
+  int fcap = o.frontier_cap ? o.frontier_cap : (qpc >= 4 ? 128 : small ? 320 : 704);
   // a multiple of 64, at least 64: a sweep stages the active items of 64
   // consecutive items at once, which must fit an empty list
   fcap = (fcap + 63) / 64 * 64;

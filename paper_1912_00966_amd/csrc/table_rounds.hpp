@@ -24,9 +24,9 @@
 //     a round later.
 // Measured against the rounds with a take pass (relax.hpp's run_rounds, which
 // the slab store, virtual warps and two or three types per lane still use): a
-// round of a query alone on its CU 1.9 us instead of 2.9 (city of 50,000 stops),
-// 256 queries on it 183 us a launch instead of 233 (1024 threads), 3,584 queries
-// over seven cities 703 us instead of 856 (768 threads, two queries a CU).
+// round of a query alone on its CU 1.8 us instead of 2.9 (city of 50,000 stops),
+// 256 queries on it 173 us a launch instead of 233 (1024 threads), 3,584 queries
+// over seven cities 675 us instead of 856 (768 threads, two queries a CU).
 #pragma once
 
 // Flags of a table slot, in its low word with the stop's number.  NEAR_A /
@@ -353,15 +353,21 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
   const int32_t wave = uniform((int32_t)(threadIdx.x >> 6));
   const int32_t fcap = topo ? 0 : a.fcap;  // a round's list that is longer is a sweep
   // The far list's entries are expanded a round after they come inside the
-  // window: a third more of it makes up for that (the rounds of city-50k are as
-  // many as with 7,200 s for every listed stop, 23.3 a query by simulation, and
-  // their type evaluations 14.1k against 13.8k).
-  const int32_t window = topo || a.window <= 0 ? 0 : (int32_t)min((int64_t)a.window + a.window / 3, (int64_t)INF);
+  // window: a sixth more of it makes up for that.  (Launch times are flat from
+  // none to a third more, 180-184 us for 256 queries on city-50k, the bus lines'
+  // best is at none to a sixth, 248-253 us against 259 at a third, and the mixed
+  // batch's at a sixth, 701 us against 725 and 714.)
+  // (A topology sweep reads every stop's flag anyway: it has no far list, and
+  // leaves the flags of the stops past the window for the next one.)
+  const int32_t window = a.window <= 0 ? 0 : (int32_t)min((int64_t)a.window + (topo ? 0 : a.window / 6), (int64_t)INF);
   const uint32_t limit = (uint32_t)(H - H / 4);
   uint32_t total = 1;  // stops in the table
   int32_t rounds = 0, nf = 0, fmin = INF;
-  int32_t n = 0, types = 0, nw = 0, thr = INF;  // of the round's list: entries, types, windows
-  bool scan = false, ok_query = true;
+  int32_t n = 0, types = 0, nw = 0;      // of the round's list: entries, types, windows
+  int32_t thr = INF, sweep_thr = INF;    // arrivals from here on: to the far list; left by a topology sweep
+  bool scan = false;  // the far list holds arrivals inside the window
+  bool ended = false;
+  int32_t maxf = 1;
 
   // The round's halves and counters: list and marks by rounds & 1, counters
   // (of the last round, of this one, of the next one) by three in turn.
@@ -385,34 +391,35 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
     asm volatile("" : "+v"(last_near.x), "+v"(last_near.y), "+v"(last_near.z), "+v"(last_near.w));
     asm volatile("" : "+v"(last_far.x), "+v"(last_far.y), "+v"(last_far.z), "+v"(last_far.w));
   };
+  // (In vector registers: a value that every lane computes alike costs one
+  // instruction there, and two or three with scalar conditions.)
   auto decide = [&]() -> bool {
-    const uint32_t fresh = (uint32_t)uniform(last_near.w);
-    nf = min(nf + uniform(last_far.x), farcap);
-    fmin = min(fmin, uniform(last_far.z));
-    if constexpr (GOAL) bound = min(bound, uniform(last_far.w));
-    total += fresh;
-    const int32_t near_min = uniform(last_near.z), base = n > 0 ? near_min : fmin;
-    bool over = total > limit;  // or a stop found no slot: kTableFull is past any number of slots
-    ok_query = !over;
-    over = over || (n == 0 && nf == 0);
+    nf = min(nf + last_far.x, farcap);
+    fmin = min(fmin, last_far.z);
+    if constexpr (GOAL) bound = min(bound, last_far.w);
+    total += (uint32_t)last_near.w;
+    const int32_t base = n > 0 ? last_near.z : fmin;
+    const bool full = total > limit;  // or a stop found no slot: kTableFull is past any number of slots
+    bool over = full || (n | nf) == 0;
     // nothing listed can lead to an earlier arrival at the target
     if constexpr (GOAL) over = over || min(base, nf > 0 ? fmin : INF) >= bound;
-    if (!over && rounds >= max_rounds) {
-      qs.status = EAT_ERR_NOT_CONVERGED;
-      over = true;
+    maxf = max(maxf, n + nf);
+    thr = window > 0 ? min(base, INF - window) + window : INF;
+    scan = nf > 0 && fmin < thr;
+    if (topo) {
+      sweep_thr = thr;
+      thr = INF;
     }
     ++rounds;
-    qs.maxf = max(qs.maxf, n + nf);
-    thr = (window <= 0 || base >= INF - window) ? INF : base + window;
-    scan = nf > 0 && fmin < thr;
-    return !over;
+    ended = uniform(over ? 1 : 0) != 0;
+    return !ended && rounds <= max_rounds;
   };
   // The end of a round: the next round's counters are reset, the far list's
   // entries that have come inside the window move to the near list (the others
   // to the far list's other buffer), and the roles change.
   auto finish = [&]() {
     if (threadIdx.x == B - 1) *r2 = RoundCtr{{0ull, INF, 0u}, {0ull, INF, (uint32_t)INF}};
-    if (scan) {
+    if (uniform(scan ? 1 : 0) != 0) {
       TablePush P = pushes();
       for (int32_t i = (kWaves - 1 - wave) * 64 + lane; i < nf; i += B) {
         const int2 f = far0[i];
@@ -487,24 +494,29 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
       };
       if (hot) {
         if (w < nw) {
+          // before the waves that scan, fill or end a round (1,000 goal-directed
+          // queries, two on a CU: 284 -> 278 us; one on a CU: 173 -> 170)
+          __builtin_amdgcn_s_setprio(2);
           do {
             if (w != wave) read_marks();
             issue();
             if (w == wave) go = decide();
-            if (go) {
-              TablePush P = pushes();
-              table_relax<KIND, GOAL>(G, S, t, thr, bound, target, P, c);
-            }
-            wait_vector_memory<0>();
+            // the query's end included: the reads are waited for on every path, so
+            // that none of them is in flight where the next window's are issued
+            t.ok = t.ok && go;
+            TablePush P = pushes();
+            table_relax<KIND, GOAL>(G, S, t, thr, bound, target, P, c);
             w += kWaves;
           } while (go && w < nw);
+          __builtin_amdgcn_s_setprio(0);
         } else {
           go = decide();
         }
         if (go) {
           // a wave with fewer windows than wave 0 issues part of the slab's fill meanwhile
-          const int32_t most = (nw + kWaves - 1) / kWaves, mine = nw > wave ? (nw - wave + kWaves - 1) / kWaves : 0;
-          if (most > mine) fill_issue(sh, min(kFillPerStep * (most - mine), 2 * kFillPerStep));
+          // (w - wave: the types of its windows' rows; two steps' worth at most)
+          const int32_t left = nw - (w - wave);
+          if (left > 0) fill_issue(sh, left > kWaves ? 2 * kFillPerStep : kFillPerStep);
           finish();
         }
       }
@@ -534,6 +546,13 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
           beg = rg.x;
           cnt = rg.y;
           x = (int32_t)(e >> 32);
+          if (x >= sweep_thr) {
+            act = false;
+            if (!(atomicOr(S.lo(i0 + lane), P.flag) & P.flag)) {
+              atomicAdd(&r1->near.cx, 1ull);
+              atomicMin(&r1->near.min, x);
+            }
+          }
         }
       } else if (lane < 4 && i0 + lane < n) {
         const int4 e = near_of(half)[i0 + lane];
@@ -581,7 +600,10 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
     }
     finish();
   }
+  const bool ok_query = uniform(total > limit ? 1 : 0) == 0;
+  if (!ended) qs.status = EAT_ERR_NOT_CONVERGED;  // the limit of rounds
   qs.rounds += rounds - 1;  // the last decision began no round
+  qs.maxf = max(qs.maxf, maxf);
   reached = (int32_t)total;
   return ok_query;
 }

@@ -12,100 +12,181 @@ namespace {
 // Parents.  The arrival arr[v] (v != s) of an EAT answer is realised by a
 // connection (u, v, t, lam) with arr[u] <= t and t + lam == arr[v].  Within a
 // connection type (u, v, lam) the only candidate is its first departure at or
-// after arr[u]: a later one arrives later.  Each reached stop u checks its
-// types; the realising one with the smallest (u, lam) wins one 64-bit atomic
-// minimum on key[v] = u << 32 | lam.
+// after arr[u]: a later one arrives later.  The parent is the realising one with
+// the smallest (u, lam).
+//
+// The answer array is its own scratch: par[3v ..] starts as -1 three times, a
+// first pass over the reached stops' types takes the unsigned minimum of u on
+// par[3v], a second one, over the types whose tail won, that of lam on par[3v + 2]
+// and the maximum of t = arr[v] - lam on par[3v + 1].
+//
+// What bounds it is latency: a few hundred to a few thousand of the stops are
+// reached, each with some fifteen types of three dependent reads.  A wave takes
+// 16 stops and spreads the types of the reached ones over its lanes, 16 lanes a
+// stop, so that no lane has more than a few in a row (one thread per stop walked
+// all of a stop's types, 12 us on city-50k; both passes together take 7).
 // ---------------------------------------------------------------------------
-template <int KIND>
-__global__ void k_parents(GraphDev Gd, const int32_t *arr, int32_t s, unsigned long long *key) {
+constexpr int kParentStops = 16;  // stops of a wave
+
+template <int KIND, bool LAM>
+__global__ __launch_bounds__(256) void k_parents(GraphDev Gd, const int32_t *arr, int32_t s, int32_t *par) {
+  __shared__ int4 todo[256 / 64][kParentStops];  // {u, arr[u], first type, type count}
   const GraphG G = graph_g(Gd);
   gp<const int32_t> A = (gp<const int32_t>)arr;
-  const int32_t V = G.n_vertices;
-  for (int32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < V; u += gridDim.x * blockDim.x) {
-    const int32_t x = A[u];
-    if (x == INF) continue;
+  const int lane = __lane_id(), wave = threadIdx.x >> 6;
+  const int64_t u64 = ((int64_t)blockIdx.x * (256 / 64) + wave) * kParentStops + lane;
+  const bool mine = lane < kParentStops && u64 < G.n_vertices;
+  const int32_t u = mine ? (int32_t)u64 : 0;
+  const int32_t x = mine ? A[u] : INF;
+  const uint64_t m = __ballot(x != INF);
+  if (m == 0) return;
+  if (x != INF) {
     const int2 r = G.vt[u];
-    for (int32_t j = r.x; j < r.x + r.y; ++j) {
+    todo[wave][__popcll(m & ((1ull << lane) - 1ull))] = make_int4(u, x, r.x, r.y);
+  }
+  __builtin_amdgcn_wave_barrier();  // one wave's LDS operations stay in order
+  const int32_t n = (int32_t)__popcll(m);
+  for (int32_t i = lane >> 4; i < n; i += 4) {
+    const int4 e = todo[wave][i];
+    for (int32_t j = e.z + (lane & 15); j < e.z + e.w; j += 16) {
       int4 rec;
       if constexpr (KIND == kKindGrid) rec = G.side[j];  // {v, lam, ..}
       else rec = G.ty[2 * (int64_t)j];                   // {v, lam, ..}
       const int32_t v = rec.x, lam = rec.y;
+      if (v == s) continue;
       const int32_t av = A[v];
-      if (v == s || av == INF || (int64_t)x + lam > av) continue;  // no departure at or after x can realise av
+      if (av == INF || (int64_t)e.y + lam > av) continue;  // no departure at or after arr[u] can realise av
+      if constexpr (LAM) {
+        if (par[3 * (int64_t)v] != e.x) continue;  // a smaller tail realises it
+      }
       Ctr c;
-      const int32_t tc = next_departure<KIND>(G, j, r.x, r.y, x, c);
-      if (tc != INF && (int64_t)tc + lam == av)
-        atomicMin(key + v, ((unsigned long long)(uint32_t)u << 32) | (uint32_t)lam);
+      const int32_t tc = next_departure<KIND>(G, j, e.z, e.w, e.y, c);
+      if (tc == INF || (int64_t)tc + lam != av) continue;
+      if constexpr (LAM) {
+        atomicMax(par + 3 * (int64_t)v + 1, tc);
+        atomicMin(reinterpret_cast<unsigned int *>(par + 3 * (int64_t)v + 2), (unsigned int)lam);
+      } else {
+        atomicMin(reinterpret_cast<unsigned int *>(par + 3 * (int64_t)v), (unsigned int)e.x);
+      }
     }
   }
 }
 
-__global__ void k_fill_u64(unsigned long long *p, int32_t n, unsigned long long x) {
-  for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = x;
-}
-
-// par[3v .. 3v + 2] = (u, t, lam) of v's parent, or -1 three times.
-__global__ void k_parents_finish(const int32_t *arr, const unsigned long long *key, int32_t V, int32_t *par) {
-  for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < V; v += gridDim.x * blockDim.x) {
-    const unsigned long long k = key[v];
-    int32_t pu = -1, pt = -1, pl = -1;
-    if (k != ~0ull) {
-      pu = (int32_t)(k >> 32);
-      pl = (int32_t)(uint32_t)k;
-      pt = arr[v] - pl;
-    }
-    par[3 * (int64_t)v] = pu;
-    par[3 * (int64_t)v + 1] = pt;
-    par[3 * (int64_t)v + 2] = pl;
-  }
+// p[0 .. n) = x; the 16-byte stores cover what lies between 16-byte boundaries.
+__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t x) {
+  const int64_t head = min(n, (int64_t)(((16 - (reinterpret_cast<uintptr_t>(p) & 15u)) & 15u) >> 2));
+  const int64_t n4 = (n - head) >> 2, tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  gp<v4i> p4 = (gp<v4i>)(p + head);
+  const v4i x4 = {x, x, x, x};
+  for (int64_t i = tid; i < n4; i += (int64_t)gridDim.x * blockDim.x) p4[i] = x4;
+  if (tid < head) p[tid] = x;
+  const int64_t tail = head + 4 * n4 + tid;
+  if (tid < 4 && tail < n) p[tail] = x;
 }
 
 // ---------------------------------------------------------------------------
-// Profiles.  The departures of s in [lo, hi], in increasing order: one wave
-// walks them, each step taking the minimum over s's types of the next
-// departure after the previous one.  out[0..cap) receives the first cap of
-// them; info[0] = their count, info[1] = the first departure after hi (INF if
-// none).
+// Profiles.  The distinct departures of s in [lo, hi], in increasing order, by
+// one work-group: every thread walks the departures of its connection types in
+// chunks of kDepSpan seconds and sets a bit per departure in LDS; the bits'
+// prefix sum gives each departure its place.  out[0..cap) receives the first cap
+// of them; info[0] = their count, info[1] = the first departure after hi (INF if
+// none); out and info are host memory.
+//
+// What bounds it is the longest chain of one type's departures, one read each (a
+// wave that took the minimum over the types for every departure in turn made 32
+// steps of 0.7 us for 32 departures; the types' own chains are a few long).
 // ---------------------------------------------------------------------------
+constexpr int32_t kDepSpan = 1 << 17;  // seconds of a chunk: a day and a half
+constexpr int kDepBlock = 256;
+
 template <int KIND>
-__global__ __launch_bounds__(64) void k_departures(GraphDev Gd, int32_t s, int32_t lo, int32_t hi, int32_t cap,
-                                                   int32_t *out, int32_t *info) {
+__global__ __launch_bounds__(kDepBlock) void k_departures(GraphDev Gd, int32_t s, int32_t lo, int32_t hi, int32_t cap,
+                                                          int32_t *out, int32_t *info) {
+  constexpr int kWords = kDepSpan / 32;
+  __shared__ uint32_t bits[kWords];
+  __shared__ int32_t wsum[kDepBlock / 64], next;
   const GraphG G = graph_g(Gd);
   const int2 r = G.vt[s];
-  const int lane = __lane_id();
-  int32_t x = lo, k = 0, next = INF;
+  const int tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+  int32_t from = lo, found = 0;
   for (;;) {
-    int32_t best = INF;
-    for (int32_t j = r.x + lane; j < r.x + r.y; j += 64) {
-      Ctr c;
-      best = min(best, next_departure<KIND>(G, j, r.x, r.y, x, c));
+    // the chunk [from, to]
+    const int32_t to = (int64_t)from + kDepSpan - 1 < hi ? from + kDepSpan - 1 : hi;
+    const int words = ((to - from) >> 5) + 1, per = (words + kDepBlock - 1) / kDepBlock;  // per: of a thread, consecutive
+    for (int i = tid; i < words; i += kDepBlock) bits[i] = 0u;
+    if (tid == 0) next = INF;
+    __syncthreads();
+    for (int32_t j = r.x + tid; j < r.x + r.y; j += kDepBlock) {
+      int32_t x = from;
+      for (;;) {
+        Ctr c;
+        const int32_t t = next_departure<KIND>(G, j, r.x, r.y, x, c);
+        if (t == INF || t > to) {
+          atomicMin(&next, t);
+          break;
+        }
+        atomicOr(&bits[(uint32_t)(t - from) >> 5], 1u << ((uint32_t)(t - from) & 31u));
+        x = t + 1;  // t < INF
+      }
     }
-    for (int d = 32; d >= 1; d >>= 1) best = min(best, __shfl_xor(best, d));
-    if (best == INF) break;
-    if (best > hi) {
-      next = best;
-      break;
+    __syncthreads();
+    const int32_t after = next;
+    int32_t mine = 0;
+    const int w0 = min(tid * per, words), w1 = min(w0 + per, words);
+    for (int i = w0; i < w1; ++i) mine += __popc(bits[i]);
+    const int32_t incl = wave_incl_sum(mine);
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int32_t place = found + incl - mine;
+    for (int w = 0; w < kDepBlock / 64; ++w) {
+      if (w < wave) place += wsum[w];
+      found += wsum[w];
     }
-    if (lane == 0 && k < cap) out[k] = best;
-    ++k;
-    x = best + 1;  // best <= hi < INF
-  }
-  if (lane == 0) {
-    info[0] = k;
-    info[1] = next;
+    if (mine) {
+      for (int i = w0; i < w1; ++i) {
+        uint32_t b = bits[i];
+        while (b) {
+          if (place < cap) out[place] = from + i * 32 + (__ffs(b) - 1);
+          ++place;
+          b &= b - 1u;
+        }
+      }
+    }
+    if (after == INF || after > hi) {
+      if (tid == 0) {
+        info[0] = found;
+        info[1] = after;
+      }
+      return;
+    }
+    from = after;  // the next departure starts the next chunk
+    __syncthreads();
   }
 }
 
 // Row i of the k x V profile matrix keeps arr[i][v] only where it beats row
 // i + 1 (the last row: the query at the first departure after the interval,
-// `later`, or nothing when there is none); each thread walks one column.
-__global__ void k_profile_filter(int32_t *arr, const int32_t *later, int32_t k, int32_t V, int32_t s) {
+// `later`, or nothing when there is none); each thread walks one column, eight
+// rows' reads in flight at a time (one at a time the walk was a chain of k read
+// latencies: 17 us for 32 rows of city-50k, now 6).
+__global__ __launch_bounds__(256) void k_profile_filter(int32_t *arr, const int32_t *later, int32_t k, int32_t V, int32_t s) {
+  constexpr int kRows = 8;
   for (int32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < V; v += gridDim.x * blockDim.x) {
     int32_t a = arr[v];
-    for (int32_t i = 0; i < k; ++i) {
-      const int32_t b = i + 1 < k ? arr[(int64_t)(i + 1) * V + v] : (later ? later[v] : INF);
-      arr[(int64_t)i * V + v] = (v != s && a < b) ? a : INF;
-      a = b;
+    for (int32_t i0 = 0; i0 < k; i0 += kRows) {
+      int32_t b[kRows];  // rows i0 + 1 .. i0 + kRows
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        const int32_t row = i0 + 1 + i;
+        b[i] = row < k ? arr[(int64_t)row * V + v] : (row == k && later ? later[v] : INF);
+      }
+#pragma unroll
+      for (int i = 0; i < kRows; ++i) {
+        if (i0 + i < k) {
+          arr[(int64_t)(i0 + i) * V + v] = (v != s && a < b[i]) ? a : INF;
+          a = b[i];
+        }
+      }
     }
   }
 }
@@ -114,31 +195,33 @@ int blocks_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((
 
 }  // namespace
 
-hipError_t launch_parents(const GraphDev &g, int kind, const int32_t *arr, int32_t s, unsigned long long *key,
-                          int32_t *par, hipStream_t stream) {
+template <int KIND>
+static void launch_parents_kind(const GraphDev &g, const int32_t *arr, int32_t s, int32_t *par, hipStream_t stream) {
+  const unsigned blocks = (unsigned)(((int64_t)g.n_vertices + 4 * kParentStops - 1) / (4 * kParentStops));
+  hipLaunchKernelGGL((k_parents<KIND, false>), dim3(blocks), dim3(256), 0, stream, g, arr, s, par);
+  hipLaunchKernelGGL((k_parents<KIND, true>), dim3(blocks), dim3(256), 0, stream, g, arr, s, par);
+}
+
+hipError_t launch_parents(const GraphDev &g, int kind, const int32_t *arr, int32_t s, int32_t *par,
+                          hipStream_t stream) {
   const int32_t V = g.n_vertices;
   if (V <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(V)), dim3(256), 0, stream, key, V, ~0ull);
-  if (kind == kKindGrid)
-    hipLaunchKernelGGL(k_parents<kKindGrid>, dim3(blocks_for(V)), dim3(256), 0, stream, g, arr, s, key);
-  else if (kind == kKindCompact)
-    hipLaunchKernelGGL(k_parents<kKindCompact>, dim3(blocks_for(V)), dim3(256), 0, stream, g, arr, s, key);
-  else if (kind == kKindFlat)
-    hipLaunchKernelGGL(k_parents<kKindFlat>, dim3(blocks_for(V)), dim3(256), 0, stream, g, arr, s, key);
-  else
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_parents_finish, dim3(blocks_for(V)), dim3(256), 0, stream, arr, key, V, par);
+  if (kind != kKindGrid && kind != kKindCompact && kind != kKindFlat) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_fill_i32, dim3(blocks_for((3 * (int64_t)V + 3) / 4)), dim3(256), 0, stream, par, 3 * (int64_t)V, -1);
+  if (kind == kKindGrid) launch_parents_kind<kKindGrid>(g, arr, s, par, stream);
+  else if (kind == kKindCompact) launch_parents_kind<kKindCompact>(g, arr, s, par, stream);
+  else launch_parents_kind<kKindFlat>(g, arr, s, par, stream);
   return hipGetLastError();
 }
 
 hipError_t launch_departures(const GraphDev &g, int kind, int32_t s, int32_t lo, int32_t hi, int32_t cap,
                              int32_t *out, int32_t *info, hipStream_t stream) {
   if (kind == kKindGrid)
-    hipLaunchKernelGGL(k_departures<kKindGrid>, dim3(1), dim3(64), 0, stream, g, s, lo, hi, cap, out, info);
+    hipLaunchKernelGGL(k_departures<kKindGrid>, dim3(1), dim3(kDepBlock), 0, stream, g, s, lo, hi, cap, out, info);
   else if (kind == kKindCompact)
-    hipLaunchKernelGGL(k_departures<kKindCompact>, dim3(1), dim3(64), 0, stream, g, s, lo, hi, cap, out, info);
+    hipLaunchKernelGGL(k_departures<kKindCompact>, dim3(1), dim3(kDepBlock), 0, stream, g, s, lo, hi, cap, out, info);
   else if (kind == kKindFlat)
-    hipLaunchKernelGGL(k_departures<kKindFlat>, dim3(1), dim3(64), 0, stream, g, s, lo, hi, cap, out, info);
+    hipLaunchKernelGGL(k_departures<kKindFlat>, dim3(1), dim3(kDepBlock), 0, stream, g, s, lo, hi, cap, out, info);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -15,8 +15,8 @@ using eat::hip_err;
 using eat::set_err;
 
 namespace eat {
-hipError_t launch_parents(const GraphDev &g, int kind, const int32_t *arr, int32_t s, unsigned long long *key,
-                          int32_t *par, hipStream_t stream);
+hipError_t launch_parents(const GraphDev &g, int kind, const int32_t *arr, int32_t s, int32_t *par,
+                          hipStream_t stream);
 hipError_t launch_departures(const GraphDev &g, int kind, int32_t s, int32_t lo, int32_t hi, int32_t cap,
                              int32_t *out, int32_t *info, hipStream_t stream);
 hipError_t launch_profile_filter(int32_t *arr, const int32_t *later, int32_t k, int32_t V, int32_t s,
@@ -39,12 +39,7 @@ extern "C" eat_status eat_parents(const eat_graph *g, int32_t s, const int32_t *
   int kind = 0;
   st = eat::exec_kind(&g, 1, EAT_HEADERS_AUTO, &kind);
   if (st != EAT_OK) return st;
-  hipStream_t hs = static_cast<hipStream_t>(stream);
-  unsigned long long *key = nullptr;
-  HIP_TRY(hipMallocAsync(reinterpret_cast<void **>(&key), (size_t)g->info.n_vertices * 8, hs));
-  hipError_t e = eat::launch_parents(g->desc, kind, arr, s, key, par, hs);
-  const hipError_t f = hipFreeAsync(key, hs);
-  if (e == hipSuccess) e = f;
+  const hipError_t e = eat::launch_parents(g->desc, kind, arr, s, par, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_err(e, "parents launch");
   return EAT_OK;
 }

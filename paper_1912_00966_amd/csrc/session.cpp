@@ -15,6 +15,7 @@
 // Result copies: eat_session_copy records an event on the caller's stream; a
 // slot released before that event has passed keeps its slab range out of the
 // pool until it has, so no later query overwrites a slab still being copied.
+// The request loop copies all results of a poll in one launch, with one event.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,6 +31,7 @@
 #include "device.hpp"
 #include "eat.h"
 #include "internal.hpp"
+#include "slab_copy.hpp"
 
 using eat::GraphDev;
 using eat::QueryDev;
@@ -41,22 +43,30 @@ namespace {
 
 enum SlotState : int32_t { kFree = 0, kAdmitted = 1, kLaunched = 2, kDone = 3 };
 
+// An event on a copy stream that the slabs of one copy launch wait for.
+struct CopyMark {
+  hipEvent_t event = nullptr;
+  int32_t refs = 0;  // slots and deferred ranges that hold it
+};
+
 struct Slot {
   int32_t state = kFree;
   int32_t graph = 0, s = 0, ts = 0;
   int64_t off = 0;    // words into the pool
   int64_t words = 0;  // reserved words
   eat_query_stats stats{};
-  hipEvent_t copy = nullptr;  // recorded by eat_session_copy on the caller's stream
+  CopyMark *copy = nullptr;  // recorded on the caller's stream after the slab's last copy
 };
 
 struct StepBlock {
+  char *d_buf = nullptr;                // counters | bucket offsets | queries (the last two in one upload)
   QueryDev *d_q = nullptr;
   uint32_t *d_bits = nullptr;           // HBM activity bits per work-group (when they do not fit the LDS)
   int32_t *d_ctr = nullptr;
   int32_t *d_b = nullptr;               // bucket offsets
-  QueryDev *h_q = nullptr;              // pinned
-  int32_t *h_b = nullptr;               // pinned
+  char *h_buf = nullptr;                // pinned: bucket offsets | queries
+  QueryDev *h_q = nullptr;              // ... its parts
+  int32_t *h_b = nullptr;
   eat_query_stats *h_stats = nullptr;   // pinned, written by the kernel
   eat_query_stats *k_stats = nullptr;   // ... its device-side address
   int32_t *h_done = nullptr;            // pinned completion words, written by the kernel
@@ -73,7 +83,7 @@ struct StepBlock {
 // A released slot's slab range whose result copy may still be pending.
 struct Deferred {
   int64_t off, words;
-  hipEvent_t copy;
+  CopyMark *copy;
 };
 
 constexpr int64_t kSlotAlignWords = 64;  // 256-byte aligned slabs
@@ -100,7 +110,8 @@ struct eat_session {
   size_t next_block = 0;
   std::vector<size_t> order;  // in-flight blocks, oldest first
   std::vector<Deferred> deferred;
-  std::vector<hipEvent_t> spare_events;
+  std::deque<CopyMark> marks;  // all of them, at fixed addresses
+  std::vector<CopyMark *> spare_marks;
 };
 
 namespace {
@@ -112,17 +123,14 @@ void destroy(eat_session *S) {
   for (auto &b : S->blocks) {
     if (b.done) (void)hipEventDestroy(b.done);
     if (b.stream) (void)hipStreamDestroy(b.stream);
-    if (b.h_q) (void)hipHostFree(b.h_q);
-    if (b.h_b) (void)hipHostFree(b.h_b);
+    if (b.h_buf) (void)hipHostFree(b.h_buf);
     if (b.h_stats) (void)hipHostFree(b.h_stats);
     if (b.h_done) (void)hipHostFree(b.h_done);
-    if (b.d_q) (void)hipFree(b.d_q);
+    if (b.d_buf) (void)hipFree(b.d_buf);
     if (b.d_bits) (void)hipFree(b.d_bits);
   }
-  for (auto &sl : S->slots)
-    if (sl.copy) (void)hipEventDestroy(sl.copy);
-  for (auto &d : S->deferred) (void)hipEventDestroy(d.copy);
-  for (auto e : S->spare_events) (void)hipEventDestroy(e);
+  for (auto &m : S->marks)
+    if (m.event) (void)hipEventDestroy(m.event);
   if (S->d_graphs) (void)hipFree(S->d_graphs);
   if (S->d_pool) (void)hipFree(S->d_pool);
   delete S;
@@ -130,14 +138,40 @@ void destroy(eat_session *S) {
 
 void pool_give(eat_session *S, int64_t off, int64_t words);
 
+void drop_mark(eat_session *S, CopyMark *m) {
+  if (--m->refs == 0) S->spare_marks.push_back(m);
+}
+
+// A mark nobody holds; nullptr if its event cannot be made.
+CopyMark *new_mark(eat_session *S) {
+  if (!S->spare_marks.empty()) {
+    CopyMark *m = S->spare_marks.back();
+    S->spare_marks.pop_back();
+    return m;
+  }
+  S->marks.emplace_back();
+  CopyMark *m = &S->marks.back();
+  if (hipEventCreateWithFlags(&m->event, hipEventDisableTiming) != hipSuccess) {
+    S->marks.pop_back();
+    return nullptr;
+  }
+  return m;
+}
+
 // Returns to the pool the deferred ranges whose result copies have passed.
 void reclaim(eat_session *S) {
   size_t k = 0;
+  const CopyMark *seen = nullptr;  // the ranges of one launch follow each other: one query for all
+  bool passed = false;
   for (size_t i = 0; i < S->deferred.size(); ++i) {
     Deferred &d = S->deferred[i];
-    if (hipEventQuery(d.copy) == hipSuccess) {
+    if (d.copy != seen) {
+      seen = d.copy;
+      passed = hipEventQuery(d.copy->event) == hipSuccess;
+    }
+    if (passed) {
       pool_give(S, d.off, d.words);
-      S->spare_events.push_back(d.copy);
+      drop_mark(S, d.copy);
     } else {
       S->deferred[k++] = d;
     }
@@ -288,20 +322,22 @@ extern "C" eat_status eat_session_create(const eat_graph *const *graphs, int32_t
   for (auto &b : S->blocks) {
     void *p = nullptr;
     if (hipMalloc(&p, bq + 512) != hipSuccess) return fail(EAT_ERR_OUT_OF_MEMORY, "step block");
-    b.d_q = static_cast<QueryDev *>(p);
-    b.d_ctr = reinterpret_cast<int32_t *>(static_cast<char *>(p) + bq);
-    b.d_b = reinterpret_cast<int32_t *>(static_cast<char *>(p) + bq + 256);
+    b.d_buf = static_cast<char *>(p);
+    b.d_ctr = reinterpret_cast<int32_t *>(b.d_buf);
+    b.d_b = reinterpret_cast<int32_t *>(b.d_buf + 256);
+    b.d_q = reinterpret_cast<QueryDev *>(b.d_buf + 512);
     if (hipMemset(b.d_ctr, 0, 256) != hipSuccess) return fail(EAT_ERR_DEVICE, "step counters");
     if (pl.bits_global &&
         hipMalloc((void **)&b.d_bits, (size_t)S->grid_cap * (size_t)pl.bits_stride * 4) != hipSuccess)
       return fail(EAT_ERR_OUT_OF_MEMORY, "activity bits of a step");
     // statistics and completion words: coherent pinned memory the kernel writes
     const unsigned mapped = hipHostMallocMapped | hipHostMallocCoherent;
-    if (hipHostMalloc((void **)&b.h_b, 256, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&b.h_q, bq, hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc((void **)&b.h_buf, bq + 256, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&b.h_stats, bs, mapped) != hipSuccess ||
         hipHostMalloc((void **)&b.h_done, bd, mapped) != hipSuccess)
       return fail(EAT_ERR_OUT_OF_MEMORY, "pinned step staging");
+    b.h_b = reinterpret_cast<int32_t *>(b.h_buf);
+    b.h_q = reinterpret_cast<QueryDev *>(b.h_buf + 256);
     if (hipHostGetDevicePointer((void **)&b.k_stats, b.h_stats, 0) != hipSuccess ||
         hipHostGetDevicePointer((void **)&b.k_done, b.h_done, 0) != hipSuccess)
       return fail(EAT_ERR_DEVICE, "device address of pinned step memory");
@@ -390,8 +426,7 @@ static eat_status step_impl(eat_session *S, int32_t *n_launched) {
   eat::order_queries(S->graphs, qs, S->n_buckets, boff, eat::order_bands(S->plan.order, n, S->grid_cap));
   std::copy(qs.begin(), qs.end(), b.h_q);
   std::copy(boff.begin(), boff.end(), b.h_b);
-  HIP_TRY(hipMemcpyAsync(b.d_q, b.h_q, sizeof(QueryDev) * (size_t)n, hipMemcpyHostToDevice, b.stream));
-  HIP_TRY(hipMemcpyAsync(b.d_b, b.h_b, sizeof(int32_t) * boff.size(), hipMemcpyHostToDevice, b.stream));
+  HIP_TRY(hipMemcpyAsync(b.d_buf + 256, b.h_buf, 256 + sizeof(QueryDev) * (size_t)n, hipMemcpyHostToDevice, b.stream));
   RunArgs a{};
   a.graphs = S->d_graphs;
   a.queries = b.d_q;
@@ -452,14 +487,14 @@ extern "C" eat_status eat_session_copy(eat_session *S, int32_t slot, int32_t *ds
   HIP_TRY(hipMemcpyAsync(dst, src, (size_t)n * 4, hipMemcpyDefault, static_cast<hipStream_t>(stream)));
   Slot &sl = S->slots[(size_t)slot];
   if (!sl.copy) {
-    if (!S->spare_events.empty()) {
-      sl.copy = S->spare_events.back();
-      S->spare_events.pop_back();
-    } else {
-      HIP_TRY(hipEventCreateWithFlags(&sl.copy, hipEventDisableTiming));
+    try {
+      sl.copy = new_mark(S);
+    } catch (const std::bad_alloc &) {  // nothing throws across the C ABI
     }
+    if (!sl.copy) return set_err(EAT_ERR_DEVICE, "copy event");
+    sl.copy->refs = 1;
   }
-  HIP_TRY(hipEventRecord(sl.copy, static_cast<hipStream_t>(stream)));
+  HIP_TRY(hipEventRecord(sl.copy->event, static_cast<hipStream_t>(stream)));
   return EAT_OK;
 }
 
@@ -471,7 +506,8 @@ extern "C" eat_status eat_session_query_stats(eat_session *S, int32_t slot, eat_
   return EAT_OK;
 }
 
-extern "C" eat_status eat_session_release(eat_session *S, int32_t slot) {
+// Frees a slot.  copying: its result copy has only just been enqueued.
+static eat_status release_slot(eat_session *S, int32_t slot, bool copying) {
   if (!S) return set_err(EAT_ERR_INVALID_ARGUMENT, "session is NULL");
   if (slot < 0 || slot >= (int32_t)S->slots.size()) return set_err(EAT_ERR_INVALID_ARGUMENT, "slot out of range");
   Slot &sl = S->slots[(size_t)slot];
@@ -484,17 +520,20 @@ extern "C" eat_status eat_session_release(eat_session *S, int32_t slot) {
   // a finished slot may still be listed as finished if it was never polled
   auto f = std::find(S->finished.begin(), S->finished.end(), slot);
   if (f != S->finished.end()) S->finished.erase(f);
-  if (sl.copy && hipEventQuery(sl.copy) == hipErrorNotReady) {
+  if (sl.copy && (copying || hipEventQuery(sl.copy->event) == hipErrorNotReady)) {
     // a result copy may still read the slab: keep the range until it has passed
     S->deferred.push_back(Deferred{sl.off, sl.words, sl.copy});
-    sl.copy = nullptr;
   } else {
     pool_give(S, sl.off, sl.words);
+    if (sl.copy) drop_mark(S, sl.copy);
   }
+  sl.copy = nullptr;
   sl.state = kFree;
   S->free_ids.push_back(slot);
   return EAT_OK;
 }
+
+extern "C" eat_status eat_session_release(eat_session *S, int32_t slot) { return release_slot(S, slot, false); }
 
 extern "C" void eat_session_free(eat_session *S) { destroy(S); }
 
@@ -503,6 +542,49 @@ extern "C" void eat_session_free(eat_session *S) { destroy(S); }
 // admission, steps by the batching policy, completions polled, copied and
 // released.
 // ---------------------------------------------------------------------------
+// Copies and releases finished slots: the copies to memory of this device in one
+// launch per kCopySlabs of them, with one event at their end (*last: its mark,
+// one reference of the caller's), any other copy by itself.
+static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t n, const int32_t *req_of,
+                                   int32_t *const *copy_dst, void *stream, const std::vector<char> &local,
+                                   CopyMark **last) {
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  eat::CopyList list{};
+  CopyMark *mark = nullptr;
+  for (int32_t j = 0; j < n; ++j) {
+    const int32_t r = req_of[slots[j]];
+    if (!copy_dst || !copy_dst[r]) continue;
+    Slot &sl = S->slots[(size_t)slots[j]];
+    if (!local[(size_t)r]) {
+      const eat_status st = eat_session_copy(S, slots[j], copy_dst[r], stream);
+      if (st != EAT_OK) return st;
+      continue;
+    }
+    if (!mark && !(mark = new_mark(S))) return set_err(EAT_ERR_DEVICE, "copy event");
+    list.e[list.n++] = eat::SlabCopy{S->d_pool + sl.off, copy_dst[r], S->graphs[(size_t)sl.graph]->info.n_vertices};
+    sl.copy = mark;
+    ++mark->refs;
+    if (list.n == eat::kCopySlabs) {
+      const hipError_t e = eat::launch_copy_slabs(list, hs);
+      if (e != hipSuccess) return hip_err(e, "result copies");
+      list.n = 0;
+    }
+  }
+  if (mark) {
+    const hipError_t e = eat::launch_copy_slabs(list, hs);
+    if (e != hipSuccess) return hip_err(e, "result copies");
+    HIP_TRY(hipEventRecord(mark->event, hs));
+    if (*last) drop_mark(S, *last);
+    ++mark->refs;
+    *last = mark;
+  }
+  for (int32_t j = 0; j < n; ++j) {
+    const eat_status st = release_slot(S, slots[j], mark && S->slots[(size_t)slots[j]].copy == mark);
+    if (st != EAT_OK) return st;
+  }
+  return EAT_OK;
+}
+
 static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, const int32_t *src,
                              const int32_t *ts, const double *arrival_s, int32_t min_batch, double max_delay_s,
                              int32_t *const *copy_dst, void *copy_stream, double *latency_s,
@@ -527,6 +609,17 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
     if (!(arrival_s[i] >= 0.0) || (i > 0 && arrival_s[i] < arrival_s[i - 1]))
       return set_err(EAT_ERR_INVALID_ARGUMENT, "arrival_s must be >= 0 and non-decreasing");
   }
+  // which results go to memory of this device
+  std::vector<char> local((size_t)n, 0);
+  if (copy_dst)
+    for (int32_t i = 0; i < n; ++i) {
+      if (!copy_dst[i]) continue;
+      hipPointerAttribute_t at{};
+      if (hipPointerGetAttributes(&at, copy_dst[i]) == hipSuccess)
+        local[(size_t)i] = at.type == hipMemoryTypeDevice && at.device == S->device;
+      else
+        (void)hipGetLastError();  // ordinary host memory
+    }
   using Clock = std::chrono::steady_clock;
   const Clock::time_point t0 = Clock::now();
   auto now_s = [&]() { return std::chrono::duration<double>(Clock::now() - t0).count(); };
@@ -534,6 +627,20 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
   std::deque<std::pair<int32_t, double>> pending;   // admitted, not launched: (slot, admit time)
   std::vector<int32_t> req_of(S->slots.size(), -1);  // slot -> request
   std::vector<int32_t> fin(1024);
+  // Finished slots whose results are not copied yet.  One copy launch is in
+  // flight at a time: what finishes meanwhile goes with the next one, so that a
+  // burst makes a few launches and events, not one per poll (96 queries, 30
+  // polls with results: the events alone kept the copy stream busy for 0.2 ms
+  // after the last query).  No slot waits longer than that launch.
+  std::vector<int32_t> to_copy;
+  CopyMark *last = nullptr;
+  struct LastMark {  // the loop's own reference ends with it
+    eat_session *S;
+    CopyMark *&m;
+    ~LastMark() {
+      if (m) drop_mark(S, m);
+    }
+  } last_guard{S, last};
   int64_t unfinished = 0, steps = 0, launched = 0, busy = 0;
   int32_t done = 0, next = 0;
   while (done < n) {
@@ -571,19 +678,21 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
     if (nf > 0) {
       const double t_done = now_s();
       for (int32_t j = 0; j < nf; ++j) {
-        const int32_t slot = fin[(size_t)j];
-        const int32_t r = req_of[(size_t)slot];
-        req_of[(size_t)slot] = -1;
+        const int32_t r = req_of[(size_t)fin[(size_t)j]];
         latency_s[r] = t_done - arrival_s[r];
-        if (copy_dst && copy_dst[r]) {
-          st = eat_session_copy(S, slot, copy_dst[r], copy_stream);
-          if (st != EAT_OK) return st;
-        }
-        st = eat_session_release(S, slot);
-        if (st != EAT_OK) return st;
-        --unfinished;
-        ++done;
       }
+      to_copy.insert(to_copy.end(), fin.begin(), fin.begin() + nf);
+      unfinished -= nf;
+    }
+    if (!to_copy.empty() &&
+        (unfinished == 0 || !waiting.empty() || (int32_t)to_copy.size() >= eat::kCopySlabs || !copy_dst || !last ||
+         hipEventQuery(last->event) != hipErrorNotReady)) {
+      const int32_t k = (int32_t)to_copy.size();
+      st = copy_and_release(S, to_copy.data(), k, req_of.data(), copy_dst, copy_stream, local, &last);
+      if (st != EAT_OK) return st;
+      for (int32_t j = 0; j < k; ++j) req_of[(size_t)to_copy[(size_t)j]] = -1;
+      done += k;
+      to_copy.clear();
     } else if (unfinished == 0 && pending.empty() && waiting.empty() && next < n) {
       const double gap = arrival_s[next] - now_s();  // idle until the next arrival
       if (gap > 200e-6) std::this_thread::sleep_for(std::chrono::duration<double>(gap - 100e-6));

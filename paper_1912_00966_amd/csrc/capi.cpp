@@ -249,6 +249,34 @@ GraphBytes graph_bytes(const eat_layout &L, bool with_grid) {
   return b;
 }
 
+void free_scratch(eat::CallScratch &s) {
+  if (s.done) (void)hipEventDestroy(s.done);
+  if (s.host) (void)hipHostFree(s.host);
+  if (s.dev) (void)hipFree(s.dev);
+  s.done = nullptr;
+  s.host = s.dev = nullptr;
+}
+
+// The graph's call scratch; without it (no memory) the calls allocate their own.
+void make_scratch(eat_graph *g) {
+  eat::CallScratch &s = g->scratch;
+  const size_t up = align_up(eat::kScratchUpload);
+  const size_t row = align_up((size_t)std::max(g->info.n_vertices, 1) * sizeof(int32_t));
+  void *d = nullptr, *h = nullptr, *hd = nullptr;
+  if (hipMalloc(&d, up + row) == hipSuccess) s.dev = static_cast<char *>(d);
+  if (s.dev && hipHostMalloc(&h, up + eat::kScratchOut, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+    s.host = static_cast<char *>(h);
+  if (!s.host || hipHostGetDevicePointer(&hd, h, 0) != hipSuccess ||
+      hipEventCreateWithFlags(&s.done, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    free_scratch(s);
+    return;
+  }
+  s.row = reinterpret_cast<int32_t *>(s.dev + up);
+  s.out = reinterpret_cast<int32_t *>(s.host + up);
+  s.out_dev = reinterpret_cast<int32_t *>(static_cast<char *>(hd) + up);
+}
+
 }  // namespace
 
 extern "C" eat_status eat_graph_upload(const eat_layout *L, const eat_build_options *opt, void *stream,
@@ -376,6 +404,7 @@ extern "C" eat_status eat_graph_upload(const eat_layout *L, const eat_build_opti
     delete g;
     return hip_err(ue, "graph upload");
   }
+  make_scratch(g);
   *out = g;
   return EAT_OK;
 }
@@ -414,6 +443,7 @@ extern "C" void eat_graph_free(eat_graph *g) {
   (void)hipSetDevice(g->device);
   (void)hipDeviceSynchronize();
   (void)hipFree(g->d_buf);
+  free_scratch(g->scratch);
   (void)hipSetDevice(cur);
   delete g;
 }
@@ -705,11 +735,9 @@ extern "C" eat_status eat_query_goal(const eat_graph *g, int32_t s, int32_t ts, 
 // batches
 // ---------------------------------------------------------------------------
 // q_dst (nullable): per query a destination, or -1 for every stop.
-static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph,
-                               const int32_t *q_src, const int32_t *q_ts, const int32_t *q_dst, int32_t n_q,
-                               int32_t *const *arr, const eat_run_options *ro, eat_batch **out) {
-  if (!out) return set_err(EAT_ERR_INVALID_ARGUMENT, "out is NULL");
-  *out = nullptr;
+eat_status eat::plan_batch(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph,
+                           const int32_t *q_src, const int32_t *q_ts, const int32_t *q_dst, int32_t n_q,
+                           int32_t *const *arr, const eat_run_options *ro, BatchPlan *out) {
   if (!graphs || n_graphs < 1) return set_err(EAT_ERR_INVALID_ARGUMENT, "need at least one graph");
   if (n_q < 0) return set_err(EAT_ERR_INVALID_ARGUMENT, "n_q must be >= 0");
   if (n_q > 0 && (!q_graph || !q_src || !q_ts || !arr))
@@ -722,7 +750,8 @@ static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs,
     if (graphs[i]->device != dev)
       return set_err(EAT_ERR_INVALID_ARGUMENT, "graph " + std::to_string(i) + " lives on another device");
   }
-  std::vector<QueryDev> qs((size_t)n_q);
+  std::vector<QueryDev> &qs = out->qs;
+  qs.resize((size_t)n_q);
   bool goal = false;
   for (int32_t i = 0; i < n_q; ++i) {
     const int32_t gi = q_graph[i];
@@ -741,15 +770,16 @@ static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs,
   }
   // no options: the tuned record for this device, graph set and batch size,
   // else the defaults
-  eat_run_options chosen{};
+  eat_run_options &chosen = out->chosen;
+  chosen = eat_run_options{};
   if (ro) chosen = *ro;
   else if (!eat::tuned_options(dev, graphs, n_graphs, n_q, &chosen)) chosen = eat::default_batch_options(dev, n_q, max_v);
   if (goal && !ro && chosen.threads_per_vertex != 0) chosen = eat::default_batch_options(dev, n_q, max_v);
-  Plan pl;
+  Plan &pl = out->pl;
   eat_status st = make_plan(&chosen, max_v, dev, &pl);
   if (st != EAT_OK) return st;
   if (goal && (st = goal_plan(&pl)) != EAT_OK) return st;
-  int kind = 0;
+  int &kind = out->kind;
   st = eat::exec_kind(graphs, n_graphs, pl.headers, &kind);
   if (st != EAT_OK) return st;
   DeviceLimits lim;
@@ -757,10 +787,28 @@ static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs,
   if (st != EAT_OK) return st;
   const int per_cu = std::max(1, eat::relax_blocks_per_cu(pl.tpv, pl.ub, kind, pl.block, pl.lds, goal));
   const int slots = lim.cus * per_cu;  // work-groups in flight
-  std::vector<int32_t> boff;
   eat::order_queries(std::vector<const eat_graph *>(graphs, graphs + n_graphs), qs,
-                     std::min(lim.xccs, eat::kMaxBuckets), boff, eat::order_bands(pl.order, n_q, slots));
+                     std::min(lim.xccs, eat::kMaxBuckets), out->boff, eat::order_bands(pl.order, n_q, slots));
+  out->grid = std::max(1, std::min<int>(n_q, slots));
+  out->goal = goal;
+  return EAT_OK;
+}
+
+static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph,
+                               const int32_t *q_src, const int32_t *q_ts, const int32_t *q_dst, int32_t n_q,
+                               int32_t *const *arr, const eat_run_options *ro, eat_batch **out) {
+  if (!out) return set_err(EAT_ERR_INVALID_ARGUMENT, "out is NULL");
+  *out = nullptr;
+  eat::BatchPlan bp;
+  const eat_status st = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, q_dst, n_q, arr, ro, &bp);
+  if (st != EAT_OK) return st;
+  const std::vector<QueryDev> &qs = bp.qs;
+  const std::vector<int32_t> &boff = bp.boff;
+  const Plan &pl = bp.pl;
+  const bool goal = bp.goal;
   const int nb = (int)boff.size() - 1;
+  int dev = -1;
+  HIP_TRY(hipGetDevice(&dev));
 
   eat_batch *b = new (std::nothrow) eat_batch();
   if (!b) return set_err(EAT_ERR_OUT_OF_MEMORY, "host allocation failed");
@@ -768,16 +816,16 @@ static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs,
   b->n_q = n_q;
   b->tpv = pl.tpv;
   b->ub = pl.ub;
-  b->kind = kind;
+  b->kind = bp.kind;
   b->block = pl.block;
   b->lds = pl.lds;
-  b->options = chosen;
+  b->options = bp.chosen;
   const size_t b_g = align_up((size_t)n_graphs * sizeof(GraphDev));
   const size_t b_q = align_up(std::max<size_t>((size_t)n_q, 1) * sizeof(QueryDev));
   const size_t b_s = align_up(std::max<size_t>((size_t)n_q, 1) * sizeof(eat_query_stats));
   const size_t b_c = align_up(eat::kCounterWords * sizeof(int32_t));
   const size_t b_b = align_up(boff.size() * sizeof(int32_t));
-  const int grid = std::max(1, std::min<int>(n_q, slots));
+  const int grid = bp.grid;
   const size_t b_bits = pl.bits_global ? align_up((size_t)grid * (size_t)pl.bits_stride * 4) : 0;
   const size_t b_t = goal ? align_up((size_t)n_q * sizeof(int32_t)) : 0;  // destinations, in query order
   hipError_t e = hipMalloc(&b->d_buf, b_g + b_q + b_s + b_c + b_b + b_bits + b_t);
@@ -868,6 +916,50 @@ extern "C" eat_status eat_batch_run(eat_batch *b, void *stream) {
   return EAT_OK;
 }
 
+eat_status eat::batch_status(int32_t failed) {
+  if (failed) return set_err(EAT_ERR_NOT_CONVERGED, std::to_string(failed) + " queries hit their round limit");
+  return EAT_OK;
+}
+
+bool eat::fits_scratch(const BatchPlan &bp, int32_t n_graphs) {
+  return n_graphs <= kScratchGraphs && bp.qs.size() <= (size_t)kScratchQueries && !bp.pl.bits_global && !bp.goal;
+}
+
+hipError_t eat::launch_from_scratch(const BatchPlan &bp, const eat_graph *const *graphs, int32_t n_graphs,
+                                    CallScratch *s, hipStream_t stream) {
+  constexpr size_t o_b = kScratchCounters, o_g = o_b + kScratchBuckets, o_q = o_g + kScratchGraphs * sizeof(GraphDev);
+  static_assert(kCounterWords * sizeof(int32_t) <= kScratchCounters, "launch counters");
+  static_assert((kMaxBuckets + 1) * sizeof(int32_t) <= kScratchBuckets, "bucket offsets");
+  static_assert(o_q % alignof(QueryDev) == 0 && o_g % alignof(GraphDev) == 0, "aligned parts");
+  std::memset(s->host, 0, kScratchCounters);
+  std::memcpy(s->host + o_b, bp.boff.data(), bp.boff.size() * sizeof(int32_t));
+  for (int32_t i = 0; i < n_graphs; ++i)
+    std::memcpy(s->host + o_g + (size_t)i * sizeof(GraphDev), &graphs[i]->desc, sizeof(GraphDev));
+  std::memcpy(s->host + o_q, bp.qs.data(), bp.qs.size() * sizeof(QueryDev));
+  hipError_t e = hipMemcpyAsync(s->dev, s->host, o_q + bp.qs.size() * sizeof(QueryDev), hipMemcpyHostToDevice, stream);
+  if (e != hipSuccess) return e;
+  RunArgs a{};
+  a.graphs = reinterpret_cast<const GraphDev *>(s->dev + o_g);
+  a.queries = reinterpret_cast<const QueryDev *>(s->dev + o_q);
+  a.nq = (int32_t)bp.qs.size();
+  apply_plan(bp.pl, &a);
+  a.buckets = reinterpret_cast<const int32_t *>(s->dev + o_b);
+  a.n_buckets = (int32_t)bp.boff.size() - 1;
+  a.work = reinterpret_cast<int32_t *>(s->dev);
+  a.n_failed = a.work + 1;
+  e = launch_relax(a, bp.pl.tpv, bp.pl.ub, bp.kind, bp.pl.block, bp.grid, bp.pl.lds, stream);
+  if (e != hipSuccess) return e;
+  // the last work-group has moved the count to word 2
+  return hipMemcpyAsync(s->out, a.work + 2, sizeof(int32_t), hipMemcpyDeviceToHost, stream);
+}
+
+hipError_t eat::wait_scratch(CallScratch *s, hipStream_t stream) {
+  hipError_t e = hipEventRecord(s->done, stream);
+  if (e == hipSuccess) e = hipEventSynchronize(s->done);
+  if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+  return e;
+}
+
 extern "C" eat_status eat_batch_wait(eat_batch *b, eat_query_stats *stats) {
   if (!b) return set_err(EAT_ERR_INVALID_ARGUMENT, "batch is NULL");
   if (!b->ran) {
@@ -879,8 +971,7 @@ extern "C" eat_status eat_batch_wait(eat_batch *b, eat_query_stats *stats) {
   HIP_TRY(hipMemcpy(&failed, b->args.work + 2, 4, hipMemcpyDeviceToHost));
   if (stats && b->n_q > 0)
     HIP_TRY(hipMemcpy(stats, b->args.stats, sizeof(eat_query_stats) * (size_t)b->n_q, hipMemcpyDeviceToHost));
-  if (failed) return set_err(EAT_ERR_NOT_CONVERGED, std::to_string(failed) + " queries hit their round limit");
-  return EAT_OK;
+  return eat::batch_status(failed);
 }
 
 extern "C" void eat_batch_free(eat_batch *b) {
@@ -896,6 +987,29 @@ extern "C" eat_status eat_query_batch(const eat_graph *const *graphs, int32_t n_
                                       const int32_t *q_ts, int32_t n_q, int32_t *const *arr,
                                       void *stream, const eat_run_options *ro,
                                       eat_query_stats *stats) {
+  // A batch without statistics that fits the first graph's scratch allocates
+  // nothing: one upload, one launch, one wait (allocations, five blocking copies,
+  // an event and two frees were 0.13 ms of a 0.29 ms call of 100 queries).
+  if (graphs && n_graphs >= 1 && graphs[0] && n_q > 0 && n_q <= eat::kScratchQueries && !stats) {
+    eat::ScratchLock lock(graphs[0]);
+    if (eat::CallScratch *sc = lock.get()) {
+      try {
+        eat::BatchPlan bp;
+        const eat_status st = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, nullptr, n_q, arr, ro, &bp);
+        if (st != EAT_OK) return st;
+        if (eat::fits_scratch(bp, n_graphs)) {
+          hipStream_t hs = static_cast<hipStream_t>(stream);
+          const hipError_t e = eat::launch_from_scratch(bp, graphs, n_graphs, sc, hs);
+          const hipError_t w = eat::wait_scratch(sc, hs);
+          if (e != hipSuccess) return hip_err(e, "relaxation launch");
+          if (w != hipSuccess) return hip_err(w, "batch completion");
+          return eat::batch_status(sc->out[0]);
+        }
+      } catch (const std::bad_alloc &) {  // nothing throws across the C ABI
+        return set_err(EAT_ERR_OUT_OF_MEMORY, "host allocation failed");
+      }
+    }
+  }
   eat_batch *b = nullptr;
   eat_status s = eat_batch_create(graphs, n_graphs, q_graph, q_src, q_ts, n_q, arr, ro, &b);
   if (s != EAT_OK) return s;

@@ -10,6 +10,31 @@
 #include "device.hpp"
 #include "eat.h"
 
+namespace eat {
+
+// Memory that a graph keeps for the calls that return only when their work is
+// done (one-shot batches, profiles), so that they allocate nothing: allocated
+// with the graph, freed with it.  One call at a time uses it (ScratchLock);
+// another one at the same moment, or one that needs more, allocates its own.
+constexpr int32_t kScratchQueries = 1024;
+constexpr int32_t kScratchGraphs = 16;
+// The upload of a batch: launch counters | bucket offsets | graphs | queries.
+constexpr size_t kScratchCounters = 256, kScratchBuckets = 256;
+constexpr size_t kScratchUpload =
+    kScratchCounters + kScratchBuckets + kScratchGraphs * sizeof(GraphDev) + kScratchQueries * sizeof(QueryDev);
+struct CallScratch {
+  char *dev = nullptr;       // the upload | one result row of the graph
+  int32_t *row = nullptr;    // ... its row
+  char *host = nullptr;      // pinned: the upload | {count, next} or failures, departures
+  int32_t *out = nullptr;    // ... its results, kScratchQueries + 4 words
+  int32_t *out_dev = nullptr;  // ... as the device addresses them
+  hipEvent_t done = nullptr;
+  std::mutex mu;
+};
+constexpr size_t kScratchOut = (kScratchQueries + 4) * sizeof(int32_t);
+
+}  // namespace eat
+
 struct eat_graph {
   int device = 0;
   eat_graph_info_t info{};
@@ -19,6 +44,7 @@ struct eat_graph {
   std::mutex mu;                   // guards the single-query scratch
   eat_query_stats *d_stats = nullptr;
   int32_t *d_failed = nullptr;
+  eat::CallScratch scratch;
   std::vector<int32_t> rank;       // position of each stop in the layout order
 };
 
@@ -85,6 +111,52 @@ struct Plan {
 eat_status exec_kind(const eat_graph *const *g, int32_t n, int headers, int *kind);
 // max_v: the largest graph the kernel will see.
 eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan *pl);
+// A graph's scratch for one call: held while this object lives, if it is there
+// and free.
+class ScratchLock {
+ public:
+  explicit ScratchLock(const eat_graph *g) {
+    CallScratch &s = const_cast<eat_graph *>(g)->scratch;
+    if (s.dev && s.mu.try_lock()) s_ = &s;
+  }
+  ~ScratchLock() {
+    if (s_) s_->mu.unlock();
+  }
+  ScratchLock(const ScratchLock &) = delete;
+  ScratchLock &operator=(const ScratchLock &) = delete;
+  CallScratch *get() const { return s_; }
+
+ private:
+  CallScratch *s_ = nullptr;
+};
+
+// A batch checked, planned and put in launch order (capi.cpp).
+struct BatchPlan {
+  std::vector<QueryDev> qs;
+  std::vector<int32_t> boff;  // bucket offsets
+  Plan pl;
+  eat_run_options chosen{};
+  int kind = 0;
+  int grid = 1;
+  bool goal = false;
+};
+// May throw std::bad_alloc.
+eat_status plan_batch(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph, const int32_t *q_src,
+                      const int32_t *q_ts, const int32_t *q_dst, int32_t n_q, int32_t *const *arr,
+                      const eat_run_options *ro, BatchPlan *out);
+// True if a planned batch of n_graphs graphs fits a graph's scratch.
+bool fits_scratch(const BatchPlan &bp, int32_t n_graphs);
+// Enqueues a planned batch on the stream from a graph's scratch: one upload, one
+// launch, and the count of queries that hit their round limit to scratch
+// out[0].  No statistics.  The caller waits before it gives the scratch back,
+// also when this fails.
+hipError_t launch_from_scratch(const BatchPlan &bp, const eat_graph *const *graphs, int32_t n_graphs, CallScratch *s,
+                               hipStream_t stream);
+// Waits for what was enqueued on the stream from a scratch (its event).
+hipError_t wait_scratch(CallScratch *s, hipStream_t stream);
+// The result of a finished batch by its count of failures.
+eat_status batch_status(int32_t failed);
+
 // RunArgs fields that come from a plan.
 void apply_plan(const Plan &pl, RunArgs *a);
 

@@ -409,9 +409,8 @@ eat_status eat_query_batch(const eat_graph *const *graphs, int32_t n_graphs,
  * journey that leaves s no earlier than arr[s] and arrives at arr[v]; parents
  * strictly decrease the arrival (lam >= 1), so the walk ends.  On a graph
  * built with sub-trip shortcuts a parent can be a shortcut (one vehicle's
- * ride over several stops).  Asynchronous on stream (a stream-ordered scratch
- * of 8 * n_vertices bytes).  EAT_ERR_INVALID_ARGUMENT for a NULL pointer or s
- * out of range. */
+ * ride over several stops).  Asynchronous on stream, without memory of its own.
+ * EAT_ERR_INVALID_ARGUMENT for a NULL pointer or s out of range. */
 eat_status eat_parents(const eat_graph *g, int32_t s, const int32_t *arr, int32_t *par, void *stream);
 
 /* Profile of source s over departures in [t_lo, t_hi]: the Pareto-optimal

@@ -63,6 +63,8 @@ constexpr int kClaim = 4;  // frontier entries a wave claims at a time (rounds o
 // path; larger ones fall back to claims of kClaim entries.
 constexpr int kTabWin = 80;         // table_rounds: windows of the round's list and of the next one's
 constexpr int kWin = 2 * kTabWin;   // run_rounds: one list's
+// Start marks: of each of two lists a word before the windows' and a spare one.
+constexpr int kMarkWords = 2 * (kTabWin + 2);
 // Chunks of the slab fill a lane issues per step a wave waits for others.
 constexpr int32_t kFillPerStep = 8;
 
@@ -817,8 +819,8 @@ struct Shared {
   // at type 64 w + i; wentry[w] is the X entry holding type 64 w.  A wave
   // clears the bits of each window it relaxes, so they are zero between rounds.
   // (table_rounds: two halves of kTabWin windows, used in turn; see list_near.)
-  unsigned long long wstart[2 * (kTabWin + 1)];
-  uint16_t wentry[kWin];
+  unsigned long long wstart[kMarkWords];
+  uint16_t wentry[kWin + 2];
   RoundCtr rc[3];
   // the infinity fill of the result slab still to issue: 16-byte chunks
   // [fill_next, fill_n4) of fill_p (table queries; see fill_idle)
@@ -1274,7 +1276,7 @@ __device__ __forceinline__ void slab_query(const RunArgs &a, const GraphG &G, gp
   const int32_t VW = (V + 31) >> 5;
   const FList l0{l, l + F, l + 2 * F}, l1{l + 3 * F, l + 4 * F, l + 5 * F};
   for (int32_t i = tid; i < VW; i += B) bits_st(bits, i, 0u);
-  for (int32_t i = tid; i < 2 * (kTabWin + 1); i += B) sh.wstart[i] = 0ull;  // a table that overflowed left marks
+  for (int32_t i = tid; i < kMarkWords; i += B) sh.wstart[i] = 0ull;  // a table that overflowed left marks
   if (tid == 0) {
     sh.over = 0;
     sh.fill_n4 = 0;  // the fill is complete: the slab now holds the arrivals
@@ -1369,7 +1371,7 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(
         sh.q = q;
       }
       if (tid < 5) sh.acc[tid] = 0ull;
-      if (tid < 2 * (kTabWin + 1)) sh.wstart[tid] = 0ull;
+      if (tid < kMarkWords) sh.wstart[tid] = 0ull;
       if (tid == 0) {
         sh.count = 0;
         sh.over = 0;

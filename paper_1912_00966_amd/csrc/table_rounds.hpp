@@ -2,11 +2,13 @@
 // the on-chip table, one connection type per lane (included by relax.hpp).
 //
 // What bounds it: the instructions of one wave, one after the other.  A query has
-// some tens of rounds of a few hundred connection types each; a wave alone on
-// its SIMD retires an instruction every ten cycles or so, whatever the other
-// waves do, and the barrier waits for the wave with the longest path.  So the
-// path from the barrier to the reads of the types is kept short, and no work is
-// prepared by one wave for another between two barriers:
+// some tens of rounds of a few hundred connection types each; a wave takes about
+// ten cycles an instruction whatever the other waves do (an LDS answer 65-90, a
+// condition of its lanes 25: compare, mask, branch, restore), and the barrier
+// waits for the wave with the longest path.  So the path from the barrier to the
+// reads of the types is kept short, no work is prepared by one wave for another
+// between two barriers, and lanes that have nothing to do go along (a neutral
+// operand, a spare entry at a list's end) instead of being masked:
 //   * A push books its place in the next round's list and the numbers of its
 //     connection types in one 64-bit LDS atomic of its lane (the LDS serialises
 //     the few lanes of a wave that push; a prefix sum over the wave was 30
@@ -24,9 +26,9 @@
 //     a round later.
 // Measured against the rounds with a take pass (relax.hpp's run_rounds, which
 // the slab store, virtual warps and two or three types per lane still use): a
-// round of a query alone on its CU 1.8 us instead of 2.9 (city of 50,000 stops),
-// 256 queries on it 173 us a launch instead of 233 (1024 threads), 3,584 queries
-// over seven cities 675 us instead of 856 (768 threads, two queries a CU).
+// query of 19 rounds alone on its CU 34 us instead of 54 (city of 50,000 stops),
+// 256 queries on it 155 us a launch instead of 230 (1024 threads), 3,584 queries
+// over seven cities 640 us instead of 850 (768 threads, two queries a CU).
 #pragma once
 
 // Flags of a table slot, in its low word with the stop's number.  NEAR_A /
@@ -66,22 +68,26 @@ struct TagTable {
     return lds_ld(reinterpret_cast<const int32_t *>(kv + p) + 1);
   }
   // Arrival of stop v (INF if none); pos = its slot, or the empty slot where it
-  // would go (slots are never freed), -1 if the table is full.
-  __device__ __forceinline__ int32_t find(int32_t v, int32_t &pos) const {
+  // would go (slots are never freed).  No slot left: *full is told, and the
+  // arrival is 0, which nothing improves.
+  __device__ __forceinline__ int32_t find(int32_t v, int32_t &pos, uint32_t *full) const {
     uint32_t p = home(v);
     const ulonglong2 two = *reinterpret_cast<const ulonglong2 *>(kv + p);
+    // 0: the slot is v's (the flags shifted out) or empty.  (Minima of numbers,
+    // not conditions of lanes, which pass through scalar registers.)
     const uint32_t k0 = (uint32_t)two.x, k1 = (uint32_t)two.y;
-    const bool m0 = k0 == NO_KEY || (k0 & STOP_MASK) == (uint32_t)v;
-    const bool m1 = k1 == NO_KEY || (k1 & STOP_MASK) == (uint32_t)v;
-    pos = (int32_t)(m0 ? p : p + 1u);
-    int32_t av = m0 ? (int32_t)(two.x >> 32) : (int32_t)(two.y >> 32);  // an empty slot holds INF
-    if (__builtin_expect(__ballot(!(m0 || m1)) != 0ull, 0)) {
-      if (!(m0 || m1)) {
+    const uint32_t z0 = min((k0 ^ (uint32_t)v) << 3, ~k0), z1 = min((k1 ^ (uint32_t)v) << 3, ~k1);
+    pos = (int32_t)(z0 == 0u ? p : p + 1u);
+    int32_t av = z0 == 0u ? (int32_t)(two.x >> 32) : (int32_t)(two.y >> 32);  // an empty slot holds INF
+    const uint32_t z = min(z0, z1);
+    if (__builtin_expect(__ballot(z != 0u) != 0ull, 0)) {
+      if (z != 0u) {
         ++p;
         for (uint32_t n = 2;; ++n) {
           if (n > mask) {
-            pos = -1;
-            return INF;
+            atomicOr(full, kTableFull);
+            av = 0;
+            break;
           }
           p = (p + 1u) & mask;
           const unsigned long long e = entry((int32_t)p);
@@ -96,38 +102,42 @@ struct TagTable {
     }
     return av;
   }
-  // Lowers v's arrival to cand < av (av, pos from find; pos >= 0).  True if it
-  // was lowered: item = v's slot, old = the flags it had (0 for a new stop),
-  // fresh = it is new.  full: no slot left.
-  __device__ __forceinline__ bool improve(int32_t v, int32_t pos, int32_t av, int32_t cand, uint32_t flag,
-                                          int32_t &item, uint32_t &old, bool &fresh, bool &full) const {
+  // Tries to lower v's arrival to cand < av (av, pos from find).  Returns the
+  // arrival before (cand is an improvement if it is later; INF for a new stop);
+  // item = v's slot, old = the flags it had (0 for a new stop), fresh = it is
+  // new.  No slot left: *full is told, 0 returned.
+  __device__ __forceinline__ int32_t lower(int32_t v, int32_t pos, int32_t av, int32_t cand, uint32_t flag,
+                                           int32_t &item, uint32_t &old, bool &fresh, uint32_t *full) const {
     const unsigned long long want = ((unsigned long long)(uint32_t)cand << 32) | flag | (uint32_t)v;
     item = pos;
     const bool insert = av == INF;  // every stored arrival is finite
-    // two results, so that both kinds are in flight together
-    unsigned long long wi = 0ull, wm = 0ull;
-    if (insert) wi = atomicCAS(kv + pos, EMPTY_SLOT, want);
-    if (!insert) wm = atomicMin(kv + pos, want);
-    fresh = insert && wi == EMPTY_SLOT;
+    // Every lane does both, the one that is not meant for it without effect: no
+    // slot holds all ones, and every slot is less.
+    const uint32_t meant = insert ? (uint32_t)INF : ~0u;
+    const unsigned long long wi = atomicCAS(kv + pos, ((unsigned long long)meant << 32) | NO_KEY, want);
+    const unsigned long long wm = atomicMin(kv + pos, insert ? ~0ull : want);
     old = insert ? 0u : (uint32_t)wm;
-    bool better = insert || cand < (int32_t)(wm >> 32);
+    int32_t before = insert ? INF : (int32_t)(wm >> 32);
+    fresh = insert;
     // a swap that lost a race for its slot: lower v's slot if it went there, else
     // probe on to it or to the next empty slot
-    const bool lost = insert && !fresh;
+    const bool lost = insert && wi != EMPTY_SLOT;
     if (__builtin_expect(__ballot(lost) != 0ull, 0)) {
       if (lost) {
-        better = false;
+        before = 0;
+        fresh = false;
         uint32_t p = (uint32_t)pos, key = (uint32_t)wi;
         for (uint32_t n = 0;; ++n) {
           if (n > mask) {
-            full = true;
+            atomicOr(full, kTableFull);
             break;
           }
           if (key == NO_KEY) {
             const unsigned long long c = atomicCAS(kv + p, EMPTY_SLOT, want);
             if (c == EMPTY_SLOT) {
               item = (int32_t)p;
-              fresh = better = true;
+              fresh = true;
+              before = INF;
               break;
             }
             key = (uint32_t)c;
@@ -136,7 +146,7 @@ struct TagTable {
             const unsigned long long m = atomicMin(kv + p, want);
             item = (int32_t)p;
             old = (uint32_t)m;
-            better = cand < (int32_t)(m >> 32);
+            before = (int32_t)(m >> 32);
             break;
           }
           p = (p + 1u) & mask;
@@ -144,7 +154,7 @@ struct TagTable {
         }
       }
     }
-    return better;
+    return before;
   }
 };
 
@@ -166,20 +176,20 @@ struct TablePush {
   int32_t fcap, farcap, far0;  // far0: entries the far list held when the round began
   uint32_t flag;               // the near flag of the next round
 
-  // Entry `slot` of the near list, whose types are numbered from toff on.
+  // Entry `slot` of the near list, whose types are numbered from toff on.  What
+  // lies past the list or the windows goes to the spare entry or word at their
+  // end: a lane condition costs 25 cycles, a minimum 4.
   __device__ __forceinline__ void list_near(int32_t slot, int32_t toff, int32_t item, int32_t beg, int32_t cnt) {
-    if (slot < fcap) {
-      near[slot] = make_int4(beg, cnt, toff, item);
-      // bit i of wstart[w + 1]: an entry's types start at type 64 w + i + 1
-      // (a lane counts the bits below it); word 0 takes what starts at type 0
-      const int32_t q = toff - 1, w = (q >> 6) + 1;
-      if (w <= kTabWin) atomicOr(&wstart[w], 1ull << (q & 63));
-      // the windows whose first type is one of this entry's
-      int32_t b = w;
-      if (b < kTabWin && (b << 6) < toff + cnt) wentry[b] = (uint16_t)slot;
-      if (cnt > 64)
-        while (++b < kTabWin && (b << 6) < toff + cnt) wentry[b] = (uint16_t)slot;
-    }
+    near[min(slot, fcap)] = make_int4(beg, cnt, toff, item);
+    // bit i of wstart[w + 1]: an entry's types start at type 64 w + i + 1
+    // (a lane counts the bits below it); word 0 takes what starts at type 0
+    const int32_t q = toff - 1, w = (q >> 6) + 1;
+    atomicOr(&wstart[min(w, kTabWin + 1)], 1ull << (q & 63));
+    // the windows whose first type is one of this entry's
+    wentry[(w << 6) < toff + cnt ? min(w, kTabWin) : kTabWin] = (uint16_t)slot;
+  }
+  __device__ __forceinline__ void list_more(int32_t slot, int32_t toff, int32_t cnt) {
+    for (int32_t b = ((toff - 1) >> 6) + 2; b < kTabWin && (b << 6) < toff + cnt; ++b) wentry[b] = (uint16_t)slot;
   }
   // The far list is full: the stop is expanded in the next round already.
   __device__ __forceinline__ void spill(int32_t item, int32_t beg, int32_t cnt, int32_t val) {
@@ -188,18 +198,23 @@ struct TablePush {
     const unsigned long long b = atomicAdd(&rc->near.cx, 1ull | ((unsigned long long)(uint32_t)cnt << 32));
     atomicMin(&rc->near.min, val);
     list_near((int32_t)(uint32_t)b, (int32_t)(uint32_t)(b >> 32), item, beg, cnt);
+    list_more((int32_t)(uint32_t)b, (int32_t)(uint32_t)(b >> 32), cnt);
   }
   // Lists a stop (cnt > 0 types).
   __device__ __forceinline__ void operator()(bool isfar, int32_t item, int32_t beg, int32_t cnt, int32_t val) {
     PushCtr *const t = isfar ? &rc->far : &rc->near;
     const unsigned long long b = atomicAdd(&t->cx, 1ull | ((unsigned long long)(uint32_t)(isfar ? 0 : cnt) << 32));
-    const int32_t slot = (int32_t)(uint32_t)b;
-    if (!isfar) {
-      list_near(slot, (int32_t)(uint32_t)(b >> 32), item, beg, cnt);
-    } else if (far0 + slot < farcap) {
-      far[far0 + slot] = make_int2(item | (cnt << 16), beg);
-    } else {
-      spill(item, beg, cnt, val);
+    // both lists' writes for every lane, the other list's to its spare entry
+    const int32_t slot = (int32_t)(uint32_t)b, toff = (int32_t)(uint32_t)(b >> 32);
+    const int32_t place = isfar ? far0 + slot : farcap;
+    list_near(isfar ? fcap : slot, isfar ? kTabWin * 64 + 1 : toff, item, beg, cnt);
+    far[min(place, farcap)] = make_int2(item | (cnt << 16), beg);
+    const bool rare = isfar ? place >= farcap : cnt > 64;
+    if (__builtin_expect(__ballot(rare) != 0ull, 0)) {
+      if (rare) {
+        if (isfar) spill(item, beg, cnt, val);
+        else list_more(slot, toff, cnt);
+      }
     }
   }
 };
@@ -215,12 +230,11 @@ __device__ __forceinline__ void wait_vector_memory() {
 }
 
 // A connection type on its way: its record r (and r2, grid form excepted), the
-// grid entry e of its tail stop's arrival x; ok: there is one, and a departure
-// at or after x may exist.
+// grid entry e of its tail stop's arrival x.  No type, or no departure at or
+// after x: x = INF, from which nothing improves.
 struct TypeRead {
   int4 r, r2, e;
   int32_t x;
-  bool ok;
 };
 
 // Issues the reads of the d-th type of a stop with types [b, b + n), reached at
@@ -238,13 +252,12 @@ __device__ __forceinline__ void issue_record(const GraphG &G, int32_t b, int32_t
 template <int KIND>
 __device__ __forceinline__ void issue_entry(const GraphG &G, int32_t b, int32_t n, int32_t d, int32_t x, bool in,
                                             TypeRead &t) {
-  t.x = x;
-  t.ok = in;
+  t.x = in ? x : INF;
   if constexpr (KIND == kKindGrid) {
+    t.x = x < G.horizon ? t.x : INF;
     // x < horizon <= 64 * 32767 < 2^21: x + 0.5 is exact in float and (x + 0.5) /
     // width is 2^-22 of itself or more away from every integer, more than the two
     // roundings of the product move it, so its integer part is the cluster of x
-    t.ok = in && x < G.horizon;
     const int32_t xc = min(x, G.horizon - 1);
     const uint32_t k = (uint32_t)(((float)xc + 0.5f) * G.inv_cw);
     // unconditional, so that the record and the entry are the two reads in
@@ -260,35 +273,38 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
   const int32_t x = t.x;
   Look L;
   if constexpr (KIND == kKindGrid) {
-    L.mode = t.ok ? 2 : 0;
+    L.mode = 2;
     L.e = t.e;
     wait_vector_memory<1>();
   } else {
     look_locate<KIND>(G, t.r, KIND == EAT_LAYOUT_HYBRID ? (uint32_t)t.r2.z : 0u, x, L);
-    if (!t.ok) L.mode = 0;
     look_fetch_headers<KIND>(G, t.r, L);
   }
   const int32_t v = t.r.x, lam = t.r.y;
-  int32_t pos = -1;
-  const int32_t av = S.find(v, pos);
+  int32_t pos = 0;
+  const int32_t av = S.find(v, pos, &P.rc->near.extra);
   wait_vector_memory<0>();
-  if (t.ok) c.tev++;
+  c.tev += x != INF ? 1u : 0u;
   // any departure leaves at t_c >= x, so it arrives at >= x + lam: skip the
   // type when that cannot beat arr[v] (early termination, Section III-D)
-  if (x >= av - lam || L.mode == 0) return;
+  if (x >= av - lam) return;
+  if constexpr (KIND != kKindGrid) {
+    if (L.mode == 0) return;
+  }
   count_fetch<KIND>(t.r, L, c);
   int32_t tc;
   if constexpr (KIND == kKindGrid) {
-    // look_finish of a grid entry, in the order of the forms' frequency
-    tc = t.e.x;
-    if (__builtin_expect(x > tc, 1)) {
-      if (__builtin_expect(t.e.y >= 0, 1)) {
-        const int32_t d = t.e.y & 0xffff, n = t.e.y >> 16;
-        const uint32_t r = (uint32_t)(x - t.e.x - 1);
-        const int32_t i = (int32_t)(t.e.w ? __umulhi(r, (uint32_t)t.e.w) : r) + 1;
-        tc = i < n ? t.e.x + i * d : t.e.z;
-      } else {
-        if (__builtin_expect(grid_pool_array(t.e.y), 0)) {  // more than five departures
+    // look_finish of a grid entry: the progression (also every empty cluster) is
+    // worked out for all lanes, an array only where there is one
+    const int32_t d = t.e.y & 0xffff, n = t.e.y >> 16;
+    const uint32_t r = (uint32_t)(x - t.e.x - 1), hi = __umulhi(r, (uint32_t)t.e.w);
+    const int32_t i = (int32_t)(t.e.w ? hi : r) + 1;
+    tc = i < n ? t.e.x + i * d : t.e.z;
+    tc = x <= t.e.x ? t.e.x : tc;
+    const bool array = t.e.y < 0 && x > t.e.x;
+    if (__ballot(array)) {
+      if (array) {
+        if (__builtin_expect(__ballot(grid_pool_array(t.e.y)) != 0ull, 0)) {  // more than five departures
           look_fetch_chunks<KIND>(G, x, L, c);
           wait_vector_memory<0>();
         }
@@ -301,11 +317,9 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
     tc = look_finish<KIND>(G, t.r, x, L, c);
   }
   // INF + lam is past every arrival as an unsigned number
-  const int32_t cand = (int32_t)((uint32_t)tc + (uint32_t)lam);
+  int32_t cand = (int32_t)((uint32_t)tc + (uint32_t)lam);
+  if constexpr (GOAL) cand = cand < min(bound, lds_ld((const int32_t *)&P.rc->far.extra)) ? cand : -1;
   if ((uint32_t)cand >= (uint32_t)av) return;
-  if constexpr (GOAL) {
-    if (cand >= min(bound, lds_ld((const int32_t *)&P.rc->far.extra))) return;
-  }
   int32_t beg, cnt;
   if constexpr (KIND == kKindGrid) {
     beg = t.r.z;
@@ -318,15 +332,11 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
   const uint32_t flag = isfar ? FAR_FLAG : P.flag;
   uint32_t old = 0;
   int32_t item = 0;
-  bool fresh = false, full = false, better = false;
-  if (__builtin_expect(pos >= 0, 1)) better = S.improve(v, pos, av, cand, flag, item, old, fresh, full);
-  else full = true;
-  if (fresh) atomicAdd(&P.rc->near.extra, 1u);
-  if (__builtin_expect(__ballot(full) != 0ull, 0)) {
-    if (full) atomicOr(&P.rc->near.extra, kTableFull);
-  }
-  if (!better) return;
+  bool fresh = false;
+  const int32_t before = S.lower(v, pos, av, cand, flag, item, old, fresh, &P.rc->near.extra);
+  if (cand >= before) return;
   c.imp++;
+  atomicAdd(&P.rc->near.extra, fresh ? 1u : 0u);
   if constexpr (GOAL) {
     if (v == target) {  // the target is not expanded
       atomicMin((int32_t *)&P.rc->far.extra, cand);
@@ -335,7 +345,7 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
   }
   // also for a stop that is listed already: its arrival is earlier now
   atomicMin(isfar ? &P.rc->far.min : &P.rc->near.min, cand);
-  if (!(old & flag) && cnt > 0) P(isfar, item, beg, cnt, cand);
+  if (((old & flag) | (cnt > 0 ? 0u : 1u)) == 0u) P(isfar, item, beg, cnt, cand);
 }
 
 // Rounds until no arrival improves.  On entry (thread 0's writes, no barrier
@@ -345,13 +355,14 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
 // in the table.
 template <int KIND, int B, bool GOAL>
 __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, const TagTable &S, int32_t H,
-                                             int4 *near0, int4 *near1, int2 *far0, int2 *far1, int32_t farcap,
+                                             int4 *near0, int4 *near1, int2 *far0, int2 *far1, int32_t far_entries,
                                              bool topo, int32_t max_rounds, int32_t bound, int32_t target, Shared &sh,
                                              QState &qs, int32_t &reached, Ctr &c) {
   constexpr int kWaves = B / 64;
   const int lane = __lane_id();
   const int32_t wave = uniform((int32_t)(threadIdx.x >> 6));
-  const int32_t fcap = topo ? 0 : a.fcap;  // a round's list that is longer is a sweep
+  // a round's list that is longer is a sweep; the lists' last entries are spare
+  const int32_t fcap = topo ? 0 : a.fcap - 1, farcap = far_entries - 1;
   // The far list's entries are expanded a round after they come inside the
   // window: a sixth more of it makes up for that.  (Launch times are flat from
   // none to a third more, 180-184 us for 256 queries on city-50k, the bus lines'
@@ -374,8 +385,8 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
   int32_t half = 0;
   RoundCtr *r0 = &sh.rc[2], *r1 = &sh.rc[0], *r2 = &sh.rc[1];
   auto near_of = [&](int32_t h) { return h ? near1 : near0; };
-  auto marks_of = [&](int32_t h) { return sh.wstart + (h ? kTabWin + 1 : 0); };
-  auto holders_of = [&](int32_t h) { return sh.wentry + (h ? kTabWin : 0); };
+  auto marks_of = [&](int32_t h) { return sh.wstart + (h ? kTabWin + 2 : 0); };
+  auto holders_of = [&](int32_t h) { return sh.wentry + (h ? kTabWin + 1 : 0); };
   auto flag_of = [&](int32_t h) { return h ? NEAR_B : NEAR_A; };
   auto pushes = [&]() {
     return TablePush{S,  near_of(half ^ 1), scan ? far1 : far0, marks_of(half ^ 1), holders_of(half ^ 1),
@@ -405,21 +416,22 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
     if constexpr (GOAL) over = over || min(base, nf > 0 ? fmin : INF) >= bound;
     maxf = max(maxf, n + nf);
     thr = window > 0 ? min(base, INF - window) + window : INF;
-    scan = nf > 0 && fmin < thr;
+    const int32_t what = uniform((over ? 1 : 0) | (nf > 0 && fmin < thr ? 2 : 0));
+    scan = (what & 2) != 0;
     if (topo) {
       sweep_thr = thr;
       thr = INF;
     }
     ++rounds;
-    ended = uniform(over ? 1 : 0) != 0;
+    ended = (what & 1) != 0;
     return !ended && rounds <= max_rounds;
   };
   // The end of a round: the next round's counters are reset, the far list's
   // entries that have come inside the window move to the near list (the others
   // to the far list's other buffer), and the roles change.
   auto finish = [&]() {
-    if (threadIdx.x == B - 1) *r2 = RoundCtr{{0ull, INF, 0u}, {0ull, INF, (uint32_t)INF}};
-    if (uniform(scan ? 1 : 0) != 0) {
+    if (wave == kWaves - 1) *r2 = RoundCtr{{0ull, INF, 0u}, {0ull, INF, (uint32_t)INF}};
+    if (scan) {
       TablePush P = pushes();
       for (int32_t i = (kWaves - 1 - wave) * 64 + lane; i < nf; i += B) {
         const int2 f = far0[i];
@@ -503,7 +515,7 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
             if (w == wave) go = decide();
             // the query's end included: the reads are waited for on every path, so
             // that none of them is in flight where the next window's are issued
-            t.ok = t.ok && go;
+            t.x = go ? t.x : INF;
             TablePush P = pushes();
             table_relax<KIND, GOAL>(G, S, t, thr, bound, target, P, c);
             w += kWaves;

@@ -94,3 +94,17 @@ def test_table_rounds_repeat_and_batch_agree():
         out = torch.full((q, n), -1, dtype=torch.int32, device="cuda")
         eat.eat_query_batch([g], np.zeros(q, np.int32), s, ts, [out[i] for i in range(q)], options=o)
         assert np.array_equal(out.cpu().numpy(), exp), o
+
+
+# entries of a list of 64 whose last is spare: one fewer than fit, as many, and
+# more by one or two; and of its far list of 32 (arrivals 300 s to 60,000 s apart)
+@pytest.mark.parametrize("fan", [(n, 3, s) for s, sizes in ((1, (62, 63, 64, 65)), (60000, (31, 32, 33, 34, 97)))
+                                 for n in sizes], ids=str)
+def test_table_rounds_with_lists_full_to_the_spare_entry(fan):
+    g, csa, n = _case(fan, "grid")
+    for s, ts in ((0, 0), (0, 3600), (n - 1, 40000)):
+        exp = csa.query(s, ts)
+        for o in ({"frontier_cap": 64}, {"frontier_cap": 64, "time_window": 300},
+                  {"frontier_cap": 64, "threads_per_query": 768, "time_window": 20000}):
+            print(fan, s, ts, o, flush=True)
+            assert np.array_equal(g.query(s, ts, options=o).cpu().numpy(), exp), (s, ts, o)

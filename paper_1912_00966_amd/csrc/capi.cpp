@@ -558,6 +558,11 @@ eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan 
   fcap = std::min(fcap, items);
   // work-groups that share a CU split its LDS
   const size_t budget = (small ? lim.lds / (size_t)qpc : lim.lds) - kStaticLds;
+  // two queries a CU: 320 entries where the activity bitmap leaves room for them,
+  // 256 on larger graphs (532,481 to 552,960 stops), which would not run at all
+  // (3,584 queries over seven cities: 658 us with 320, 660 with 256, and 1,033
+  // with 384, which halve the table)
+  if (!o.frontier_cap && qpc == 2 && (size_t)pl->bm_words * 4 + lists_lds(fcap) > budget) fcap = std::min(fcap, 256);
   // slab mode (no table, or a table that overflowed): one activity bit per
   // stop, in LDS while it fits, else in a region of HBM per work-group
   pl->bits_global = (size_t)pl->bm_words * 4 + lists_lds(fcap) > budget;

@@ -534,82 +534,90 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
       }
     } while (hot && go);
     if (!go) break;
-    // ---- a sweep over the slots, 64 at a time, or a list of more types than the
-    // windows hold, four entries at a time: each wave takes the stops in groups
-    // of four and spreads their types over its lanes.
+    // ---- a sweep over the slots, or a list of more types than the windows hold.
+    // A sweep lists the stops its flag marks, as many as the list takes at a time
+    // (a stop past the list keeps its flag for the next pass); a list's types are
+    // relaxed kTabWin windows at a time, with marks made from its entries.  So the
+    // waves share the types evenly here too.  (A wave that took four listed stops,
+    // or the marked ones of 64 slots, relaxed their types alone: a query through
+    // stops of 750 and 30,000 types took 391 ms, now 42; 256 queries on a flat
+    // city-50k in topology mode 1,038 us, now 472; with lists of 64 entries on its
+    // grid 613 us, now 533.)
     const bool sweep = n > fcap;
     go = decide();
     if (!go) break;
     qs.sweeps += sweep ? 1 : 0;
     TablePush P = pushes();
-    for (int32_t i = (int32_t)threadIdx.x; i < kTabWin; i += B) marks_of(half)[i + 1] = 0ull;
+    int4 *const list = near_of(half);
+    unsigned long long *const ws = marks_of(half) + 1;
+    uint16_t *const we = holders_of(half);
     const uint32_t flag = flag_of(half);
-    const int32_t per = sweep ? 64 : 4, upto = sweep ? H : n;
-    for (int32_t i0 = wave * per; i0 < upto; i0 += kWaves * per) {
-      int32_t beg = 0, cnt = 0, x = 0;
-      bool act = false;
+    const int32_t cap = a.fcap - 1;
+    for (int32_t i = (int32_t)threadIdx.x; i < kTabWin; i += B) ws[i] = 0ull;  // the pushes' marks
+    int32_t m = n;     // the list's entries, of all that there are
+    bool more = false;
+    do {
       if (sweep) {
-        const unsigned long long e = S.entry(i0 + lane);
-        const uint32_t key = (uint32_t)e;
-        act = key != NO_KEY && (key & flag) != 0u;
-        if (act) {
-          atomicAnd(S.lo(i0 + lane), ~flag);
-          const int2 rg = G.vt[key & STOP_MASK];
-          beg = rg.x;
-          cnt = rg.y;
-          x = (int32_t)(e >> 32);
-          if (x >= sweep_thr) {
-            act = false;
-            if (!(atomicOr(S.lo(i0 + lane), P.flag) & P.flag)) {
+        if (threadIdx.x == 0) sh.cx[0] = 0ull;
+        __syncthreads();
+        for (int32_t i0 = wave * 64; i0 < H; i0 += B) {
+          const int32_t item = i0 + lane;
+          const unsigned long long e = S.entry(item);
+          const uint32_t key = (uint32_t)e;
+          if (key == NO_KEY || !(key & flag)) continue;
+          const int32_t x = (int32_t)(e >> 32);
+          if (x >= sweep_thr) {  // left for the next round
+            atomicAnd(S.lo(item), ~flag);
+            if (!(atomicOr(S.lo(item), P.flag) & P.flag)) {
               atomicAdd(&r1->near.cx, 1ull);
               atomicMin(&r1->near.min, x);
             }
+            continue;
           }
+          const int2 rg = G.vt[key & STOP_MASK];
+          if (rg.y == 0) {  // flagged when it improved, but never listed: entries start at types of their own
+            atomicAnd(S.lo(item), ~flag);
+            continue;
+          }
+          const unsigned long long at = atomicAdd(&sh.cx[0], 1ull | ((unsigned long long)(uint32_t)rg.y << 32));
+          if ((int32_t)(uint32_t)at < cap) list[(uint32_t)at] = make_int4(rg.x, rg.y, (int32_t)(at >> 32), item);
         }
-      } else if (lane < 4 && i0 + lane < n) {
-        const int4 e = near_of(half)[i0 + lane];
-        act = true;
-        atomicAnd(S.lo(e.w), ~flag);
-        beg = e.x;
-        cnt = e.y;
-        x = S.value(e.w);
+        __syncthreads();
+        m = uniform((int32_t)(uint32_t)sh.cx[0]);
+        more = m > cap;
+        m = min(m, cap);
       }
-      if constexpr (GOAL) act = act && x < bound;
-      if (act) c.act++;
-      uint64_t m = __ballot(act && cnt > 0);
-      while (m) {
-        int32_t sb[4], sn[4], sx[4], eo[4], total4 = 0;  // wave-uniform
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool has = m != 0;
-          const int l = has ? __ffsll((unsigned long long)m) - 1 : 0;
-          sb[i] = __builtin_amdgcn_readlane(beg, l);
-          sn[i] = has ? __builtin_amdgcn_readlane(cnt, l) : 0;
-          sx[i] = __builtin_amdgcn_readlane(x, l);
-          eo[i] = total4;
-          total4 += sn[i];
-          m &= m - (has ? 1 : 0);
+      // one atomic books a place and the types' numbers: entries are in their order
+      const int32_t listed = m > 0 ? uniform(list[m - 1].z + list[m - 1].y) : 0, upto = (listed + 63) >> 6;
+      for (int32_t w0 = 0; w0 < upto; w0 += kTabWin) {
+        __syncthreads();  // the marks of the windows before are read
+        for (int32_t i = (int32_t)threadIdx.x; i < m; i += B) {
+          const int4 e = list[i];
+          const int32_t q = e.z - 1, w = (q >> 6) - w0;
+          if (w >= 0 && w < kTabWin) atomicOr(&ws[w], 1ull << (q & 63));
+          for (int32_t b = max(w + 1, 0); b < kTabWin && ((w0 + b) << 6) < e.z + e.y; ++b) we[b] = (uint16_t)i;
         }
-        for (int32_t k0 = 0; k0 < total4; k0 += 64) {
-          const int32_t k = k0 + lane;
-          const bool in = k < total4;
-          int32_t bi = sb[0], oi = 0, xi = sx[0], ni = sn[0];
-#pragma unroll
-          for (int i = 1; i < 4; ++i) {  // the last entry whose offset is <= k
-            const bool ge = eo[i] <= k && sn[i] > 0;
-            bi = ge ? sb[i] : bi;
-            oi = ge ? eo[i] : oi;
-            xi = ge ? sx[i] : xi;
-            ni = ge ? sn[i] : ni;
-          }
-          const int32_t d = in ? k - oi : 0;
+        __syncthreads();
+        for (int32_t w = wave; w < min(upto - w0, kTabWin); w += kWaves) {
+          const unsigned long long starts = ws[w];
+          const int32_t k = ((w0 + w) << 6) + lane;
+          const bool in = k < listed;
+          const int4 e = list[we[w] + rank_below(starts)];
+          ws[w] = 0ull;
+          const int32_t d = in ? k - e.z : 0;
           TypeRead t;
-          issue_record<KIND>(G, bi, d, t);
-          issue_entry<KIND>(G, bi, ni, d, xi, in, t);
+          issue_record<KIND>(G, e.x, d, t);
+          const int32_t x = S.value(e.w);
+          if (k == e.z) {
+            atomicAnd(S.lo(e.w), ~flag);
+            c.act++;
+          }
+          issue_entry<KIND>(G, e.x, e.y, d, x, GOAL ? in && x < bound : in, t);
           table_relax<KIND, GOAL>(G, S, t, thr, bound, target, P, c);
         }
       }
-    }
+      if (more) __syncthreads();  // before the next pass's list
+    } while (more);
     finish();
   }
   const bool ok_query = uniform(total > limit ? 1 : 0) == 0;

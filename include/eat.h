@@ -298,8 +298,9 @@ typedef struct {
   int32_t sweep_rounds;  /* of which topology sweeps */
   int32_t max_frontier;  /* largest frontier (pushes of one round) */
   int32_t reached;       /* stops with a finite arrival, the source included */
-  int32_t spilled;       /* 1 if the on-chip arrival table overflowed and the
-                            query was run again against the result slab */
+  int32_t spilled;       /* 1 if the on-chip arrival table overflowed, or its rounds hit
+                            max_rounds, and the query was run again against the result
+                            slab (the round limit applies to that run) */
   int64_t activations;   /* active stops processed */
   int64_t type_evals;    /* connection types examined */
   int64_t header_loads;  /* cluster headers read (hybrid) */

@@ -68,6 +68,7 @@ struct RunArgs {
   int32_t table_cap;         // on-chip arrival table slots (power of two), 0 = none
   int32_t table_bits;        // log2(table_cap)
   int32_t window;            // arrival window of a round in seconds, 0 = none
+  int32_t table_window;      // ... of a round of the table rounds, 0 = none
   // Queries are split into n_buckets contiguous buckets (queries[buckets[b]]
   // .. queries[buckets[b+1]-1]); work-group w takes queries from bucket
   // w % n_buckets first (work-groups are dealt to the XCDs in turn, so a

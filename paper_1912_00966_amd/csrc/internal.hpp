@@ -98,6 +98,7 @@ struct Plan {
   int table_bits = 0;
   int headers = EAT_HEADERS_AUTO;
   int window = 0;  // seconds, 0 = none
+  int table_window = 0;  // ... of the table rounds
   int block = 1024; // threads per query
   int order = EAT_ORDER_AUTO;
   bool bits_global = false;  // slab-mode activity bits in HBM (they do not fit the LDS)

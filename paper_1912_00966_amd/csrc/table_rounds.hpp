@@ -351,8 +351,11 @@ __device__ __forceinline__ void table_relax(const GraphG &G, const TagTable &S, 
 // Rounds until no arrival improves.  On entry (thread 0's writes, no barrier
 // since): the source's slot is in S with NEAR_A set; near0[0] is its entry;
 // rc[2] counts it and holds its arrival, rc[0] is reset; the source's windows
-// are marked in half 0.  Returns false if the table overflowed; reached = stops
-// in the table.
+// are marked in half 0.  reached = stops in the table.  Returns false if the table
+// overflowed or the limit of rounds was hit: the query then runs again in the
+// result slab.  (A stop that comes inside the window waits a round more here than
+// in run_rounds, so only that one tells whether a limit is enough: of 96 queries of
+// city-50k 65 took more rounds here than there, 30.3 on average against 29.5.)
 template <int KIND, int B, bool GOAL>
 __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, const TagTable &S, int32_t H,
                                              int4 *near0, int4 *near1, int2 *far0, int2 *far1, int32_t far_entries,
@@ -363,14 +366,7 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
   const int32_t wave = uniform((int32_t)(threadIdx.x >> 6));
   // a round's list that is longer is a sweep; the lists' last entries are spare
   const int32_t fcap = topo ? 0 : a.fcap - 1, farcap = far_entries - 1;
-  // The far list's entries are expanded a round after they come inside the
-  // window: a sixth more of it makes up for that.  (Launch times are flat from
-  // none to a third more, 180-184 us for 256 queries on city-50k, the bus lines'
-  // best is at none to a sixth, 248-253 us against 259 at a third, and the mixed
-  // batch's at a sixth, 701 us against 725 and 714.)
-  // (A topology sweep reads every stop's flag anyway: it has no far list, and
-  // leaves the flags of the stops past the window for the next one.)
-  const int32_t window = a.window <= 0 ? 0 : (int32_t)min((int64_t)a.window + (topo ? 0 : a.window / 6), (int64_t)INF);
+  const int32_t window = a.table_window;
   const uint32_t limit = (uint32_t)(H - H / 4);
   uint32_t total = 1;  // stops in the table
   int32_t rounds = 0, nf = 0, fmin = INF;
@@ -620,10 +616,9 @@ __device__ __forceinline__ bool table_rounds(const RunArgs &a, const GraphG &G, 
     } while (more);
     finish();
   }
-  const bool ok_query = uniform(total > limit ? 1 : 0) == 0;
-  if (!ended) qs.status = EAT_ERR_NOT_CONVERGED;  // the limit of rounds
-  qs.rounds += rounds - 1;  // the last decision began no round
-  qs.maxf = max(qs.maxf, maxf);
   reached = (int32_t)total;
-  return ok_query;
+  if (!ended) return false;  // the limit of rounds
+  qs.rounds += rounds - 1;   // the last decision began no round
+  qs.maxf = max(qs.maxf, maxf);
+  return uniform(total > limit ? 1 : 0) == 0;
 }

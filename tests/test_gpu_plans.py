@@ -55,3 +55,38 @@ def test_a_bitmap_past_the_smaller_lists_is_refused():
     with pytest.raises(eat.EatError) as ei:
         g.query(0, 0, options={"threads_per_query": 768})
     assert ei.value.status == eat.EAT_ERR_UNSUPPORTED
+
+
+@functools.lru_cache(maxsize=None)
+def _line(hops, lam, layout):
+    """A line of hops connections of lam seconds each, and a side branch at every stop."""
+    i = np.arange(hops, dtype=np.int32)
+    u, v = np.concatenate([i, i]), np.concatenate([i + 1, hops + 1 + i])
+    t = np.concatenate([1000 + i * (lam + 5)] * 2)
+    args = (u, v, t.astype(np.int32), np.full(2 * hops, lam, np.int32), 2 * hops + 1)
+    kw = {"grid": {}, "flat": {"layout": eat.EAT_LAYOUT_FLAT}}[layout]
+    return eat.eat_graph_build(*args, cluster_seconds=30000, **kw), oracle.Csa(*args)
+
+
+# hops shorter than the window, longer, and longer than any window asked for; one
+# round for every hop and one that finds nothing more to do
+@pytest.mark.parametrize("lam", [300, 9000, 50_000])
+@pytest.mark.parametrize("layout", ["grid", "flat"])
+def test_a_round_limit_of_one_per_hop_is_enough(lam, layout):
+    hops = 30
+    g, csa = _line(hops, lam, layout)
+    exp = csa.query(0, 0)
+    for o in ({}, {"threads_per_query": 768}, {"time_window": 60}, {"time_window": -1}, {"time_window": 20_000},
+              {"types_per_lane": 2}, {"table_cap": -1}, {"threads_per_vertex": 16}, {"mode": eat.EAT_MODE_TOPOLOGY}):
+        print(lam, layout, o, flush=True)
+        out, st = g.query(0, 0, options=dict(o, max_rounds=hops + 1), stats=True)
+        assert np.array_equal(out.cpu().numpy(), exp) and st["rounds"] <= hops + 1
+        with pytest.raises(eat.EatError) as ei:  # the last stop is out of reach
+            g.query(0, 0, options=dict(o, max_rounds=hops - 1), stats=True)
+        assert ei.value.status == eat.EAT_ERR_NOT_CONVERGED
+    n = 40
+    outs = torch.empty((n, g.n_vertices), dtype=torch.int32, device="cuda")
+    eat.eat_query_batch([g], np.zeros(n, np.int32), np.arange(n) % 5, np.zeros(n, np.int32), [outs[i] for i in range(n)],
+                        options={"max_rounds": hops + 1})
+    for i in range(5):
+        assert np.array_equal(outs[i].cpu().numpy(), csa.query(i, 0))

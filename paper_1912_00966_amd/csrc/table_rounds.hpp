@@ -55,10 +55,9 @@ struct TagTable {
   unsigned long long *kv;
   uint32_t mask;
   int32_t shift;
-  // Even: a stop's first two slots come in one 16-byte read, which ends nearly
-  // every probe.  (With one slot a read, some lane of a wave of 64 had to go on,
-  // and the wave with it, in more than half of the probes from a few hundred
-  // stops on.)
+  // Even: a stop's first two slots are read together, which ends nearly every
+  // probe.  (With one slot at a time, some lane of a wave of 64 had to go on, and
+  // the wave with it, in more than half of the probes from a few hundred stops on.)
   __device__ __forceinline__ uint32_t home(int32_t v) const { return (((uint32_t)v * 2654435761u) >> shift) & ~1u; }
   __device__ __forceinline__ uint32_t *lo(int32_t p) const { return reinterpret_cast<uint32_t *>(kv + p); }
   __device__ __forceinline__ unsigned long long entry(int32_t p) const {
@@ -72,13 +71,17 @@ struct TagTable {
   // arrival is 0, which nothing improves.
   __device__ __forceinline__ int32_t find(int32_t v, int32_t &pos, uint32_t *full) const {
     uint32_t p = home(v);
-    const ulonglong2 two = *reinterpret_cast<const ulonglong2 *>(kv + p);
+    // Two reads of 8 bytes, each a slot as one atomic left it: other waves write
+    // these slots meanwhile, and half a new slot beside half an old one would be
+    // another stop's arrival.  (One read of 16 bytes measured the same: 256 queries on
+    // city-50k 155.1 us, two reads 154.4; 3,584 over seven cities 647.5 and 646.5.)
+    const unsigned long long e0 = entry((int32_t)p), e1 = entry((int32_t)p + 1);
     // 0: the slot is v's (the flags shifted out) or empty.  (Minima of numbers,
     // not conditions of lanes, which pass through scalar registers.)
-    const uint32_t k0 = (uint32_t)two.x, k1 = (uint32_t)two.y;
+    const uint32_t k0 = (uint32_t)e0, k1 = (uint32_t)e1;
     const uint32_t z0 = min((k0 ^ (uint32_t)v) << 3, ~k0), z1 = min((k1 ^ (uint32_t)v) << 3, ~k1);
     pos = (int32_t)(z0 == 0u ? p : p + 1u);
-    int32_t av = z0 == 0u ? (int32_t)(two.x >> 32) : (int32_t)(two.y >> 32);  // an empty slot holds INF
+    int32_t av = z0 == 0u ? (int32_t)(e0 >> 32) : (int32_t)(e1 >> 32);  // an empty slot holds INF
     const uint32_t z = min(z0, z1);
     if (__builtin_expect(__ballot(z != 0u) != 0ull, 0)) {
       if (z != 0u) {

@@ -258,7 +258,9 @@ typedef struct {
                                  Section IV-B): 1,2,4,..,64; 0 = type windows (below) */
   int32_t mode;               /* eat_mode */
   int32_t max_rounds;         /* round limit per query; 0 = n_vertices + 2 without a time
-                                 window, 8 * n_vertices + 64 with one */
+                                 window, 8 * n_vertices + 64 with one.  A query that hits it
+                                 in the table's rounds (types_per_lane below) runs again
+                                 against the result slab, whose rounds then count */
   int32_t frontier_cap;       /* frontier list entries kept on chip, rounded up to a
                                  multiple of 64; 0 = auto */
   int32_t table_cap;          /* on-chip arrival-table slots (power of two); 0 = auto,
@@ -266,17 +268,25 @@ typedef struct {
   int32_t types_per_lane;     /* threads_per_vertex = 0: a round's connection types are
                                  numbered in list order and cut into windows of 64; each wave
                                  relaxes types_per_lane windows per step, one type of each per
-                                 lane (rounds of more than 8,192 types: each wave takes
-                                 4 * types_per_lane listed stops at a time and spreads their
-                                 types over its lanes); 1..3, 0 = 1 */
+                                 lane; 1..3, 0 = 1.  With 1 and arrivals in the on-chip
+                                 table, rounds of more than 5,120 types and sweeps are
+                                 relaxed 5,120 types at a time; else, in rounds of more
+                                 than 10,240 types, each wave takes 4 * types_per_lane
+                                 listed stops at a time and spreads their types over its
+                                 lanes */
   int32_t headers;            /* eat_headers: which form of the hybrid headers to read */
   int32_t time_window;        /* frontier rounds expand only the listed stops whose arrival
                                  is below (smallest arrival pushed for the round) + this
                                  many seconds; the others stay listed for a later round.
                                  0 = auto (7200), -1 = no window (every listed stop every
-                                 round, the schedule of Section III-B).  The answer is the
-                                 same either way; the window trades a few more rounds for
-                                 fewer re-expansions of stops whose arrival improves */
+                                 round, the schedule of Section III-B).  The rounds of the
+                                 on-chip table with one type per lane use a sixth more, at
+                                 least 200 s more, and expand a stop that has come inside
+                                 a round later; stops of more than 65,535 types, and those
+                                 for which the list of waiting stops has no room, do not
+                                 wait.  The answer is the same either way; the window
+                                 trades a few more rounds for fewer re-expansions of stops
+                                 whose arrival improves */
   int32_t threads_per_query;  /* work-group size of one query: 1024 (default); 768 or 512
                                  -- two queries share a CU, each with half of its LDS for
                                  the arrival table; 384 -- four per CU, a quarter each;
@@ -296,7 +306,10 @@ typedef struct {
   int32_t status;        /* EAT_OK or EAT_ERR_NOT_CONVERGED */
   int32_t rounds;        /* relaxation rounds until no arrival improved */
   int32_t sweep_rounds;  /* of which topology sweeps */
-  int32_t max_frontier;  /* largest frontier (pushes of one round) */
+  int32_t max_frontier;  /* largest frontier: stops listed for one round, those waiting
+                            outside its time window included (the on-chip table with one
+                            type per lane also counts waiting entries whose stop has been
+                            listed anew since, until they are next looked at) */
   int32_t reached;       /* stops with a finite arrival, the source included */
   int32_t spilled;       /* 1 if the on-chip arrival table overflowed, or its rounds hit
                             max_rounds, and the query was run again against the result

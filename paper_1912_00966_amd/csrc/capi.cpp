@@ -529,15 +529,18 @@ eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan 
     return set_err(EAT_ERR_INVALID_ARGUMENT, "threads_per_query 256, 384 and 768 run one connection type per lane");
   pl->window = o.time_window == 0 ? 7200 : (o.time_window < 0 ? 0 : o.time_window);
   // The table rounds expand a stop that was past the window a round after it has
-  // come inside, and make up for that with a sixth more of it.  (Launch times are
-  // flat from none to a third more, 180-184 us for 256 queries on city-50k, the bus
-  // lines' best is at none to a sixth, 248-253 us against 259 at a third, and the
-  // mixed batch's at a sixth, 701 us against 725 and 714.)  A topology sweep reads
-  // every stop's flag anyway: it has no far list, and leaves the flags of the stops
-  // past the window for the next one.
+  // come inside, and make up for that with a sixth more of it, at least 200 s.
+  // (Launch times are flat from none to a third more, 180-184 us for 256 queries on
+  // city-50k, the bus lines' best is at none to a sixth, 248-253 us against 259 at
+  // a third, and the mixed batch's at a sixth, 701 us against 725 and 714.  A short
+  // window lacks about the time that a round gains: at 300 s city-50k takes, with
+  // 50 and with 200 more, 648 and 510 us on the grid, 999 and 813 flat, 881 and 680
+  // with compact headers, where the rounds without a far list took 709, 955 and
+  // 821.)  A topology sweep reads every stop's flag anyway: it has no far list, and
+  // leaves the flags of the stops past the window for the next one.
   pl->table_window = pl->window;
-  if (o.mode != EAT_MODE_TOPOLOGY)
-    pl->table_window = (int)std::min<int64_t>((int64_t)pl->window + pl->window / 6, EAT_INF);
+  if (pl->window > 0 && o.mode != EAT_MODE_TOPOLOGY)
+    pl->table_window = (int)std::min<int64_t>((int64_t)pl->window + std::max(pl->window / 6, 200), EAT_INF);
   if (o.query_order < EAT_ORDER_AUTO || o.query_order > EAT_ORDER_BANDED)
     return set_err(EAT_ERR_INVALID_ARGUMENT, "unknown query order");
   pl->order = o.query_order;

@@ -626,13 +626,15 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
   std::deque<int32_t> waiting;                      // arrived, not admitted
   std::deque<std::pair<int32_t, double>> pending;   // admitted, not launched: (slot, admit time)
   std::vector<int32_t> req_of(S->slots.size(), -1);  // slot -> request
-  std::vector<int32_t> fin(1024);
-  // Finished slots whose results are not copied yet.  One copy launch is in
-  // flight at a time: what finishes meanwhile goes with the next one, so that a
-  // burst makes a few launches and events, not one per poll (96 queries, 30
-  // polls with results: the events alone kept the copy stream busy for 0.2 ms
-  // after the last query).  No slot waits longer than that launch.
-  std::vector<int32_t> to_copy;
+  // Finished slots stay in S->finished until their results are copied, so that a
+  // call that fails half way leaves them to its caller; `seen` of them have their
+  // latency.  While a copy launch is in flight, what finishes waits for the next
+  // one, so that a burst makes a few launches and events, not one per poll (96
+  // queries, 30 polls with results: the events alone kept the copy stream busy for
+  // 0.2 ms after the last query); a full list, a request without a slot, or the end
+  // of all launched queries does not let it wait.
+  size_t seen = 0;
+  std::vector<int32_t> group;
   CopyMark *last = nullptr;
   struct LastMark {  // the loop's own reference ends with it
     eat_session *S;
@@ -672,27 +674,25 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
         ++steps;
       }
     }
-    int32_t nf = 0;
-    eat_status st = eat_session_poll(S, fin.data(), (int32_t)fin.size(), &nf);
+    eat_status st = retire_ready(S);
     if (st != EAT_OK) return st;
-    if (nf > 0) {
+    if (seen < S->finished.size()) {
       const double t_done = now_s();
-      for (int32_t j = 0; j < nf; ++j) {
-        const int32_t r = req_of[(size_t)fin[(size_t)j]];
+      for (; seen < S->finished.size(); ++seen) {
+        const int32_t r = req_of[(size_t)S->finished[seen]];
         latency_s[r] = t_done - arrival_s[r];
+        --unfinished;
       }
-      to_copy.insert(to_copy.end(), fin.begin(), fin.begin() + nf);
-      unfinished -= nf;
     }
-    if (!to_copy.empty() &&
-        (unfinished == 0 || !waiting.empty() || (int32_t)to_copy.size() >= eat::kCopySlabs || !copy_dst || !last ||
+    if (seen > 0 &&
+        (unfinished == 0 || !waiting.empty() || seen >= (size_t)eat::kCopySlabs || !copy_dst || !last ||
          hipEventQuery(last->event) != hipErrorNotReady)) {
-      const int32_t k = (int32_t)to_copy.size();
-      st = copy_and_release(S, to_copy.data(), k, req_of.data(), copy_dst, copy_stream, local, &last);
+      group.assign(S->finished.begin(), S->finished.end());
+      st = copy_and_release(S, group.data(), (int32_t)group.size(), req_of.data(), copy_dst, copy_stream, local, &last);
       if (st != EAT_OK) return st;
-      for (int32_t j = 0; j < k; ++j) req_of[(size_t)to_copy[(size_t)j]] = -1;
-      done += k;
-      to_copy.clear();
+      for (const int32_t slot : group) req_of[(size_t)slot] = -1;
+      done += (int32_t)group.size();
+      seen = 0;
     } else if (unfinished == 0 && pending.empty() && waiting.empty() && next < n) {
       const double gap = arrival_s[next] - now_s();  // idle until the next arrival
       if (gap > 200e-6) std::this_thread::sleep_for(std::chrono::duration<double>(gap - 100e-6));

@@ -1,0 +1,145 @@
+"""The serving session's host code (session.cpp) against a stand-in for the device
+(native/fake_device.cpp): what the request loop does with slots that are not its
+own, and what it leaves behind when a call fails half way."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1912_00966_amd", "csrc")
+i32, i64, vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
+OK, BUSY = 0, 5  # eat_status
+
+
+class SessionOptions(ctypes.Structure):
+    _fields_ = [("pool_bytes", i64), ("n_streams", i32), ("max_step", i32), ("run", i32 * 13), ("reserved", i32 * 4)]
+
+
+class Report(ctypes.Structure):
+    _fields_ = [("steps", i64), ("launched", i64), ("busy_waits", i64), ("wall_s", ctypes.c_double)]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("fake") / "libsession_fake.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-w",
+                    "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(CSRC, "session.cpp"), os.path.join(ROOT, "tests", "native", "fake_device.cpp"),
+                    "-o", so, "-lpthread"], check=True)
+    lib = ctypes.CDLL(so)
+    lib.fake_alloc.restype, lib.fake_alloc.argtypes = vp, [ctypes.c_size_t]
+    lib.fake_graph.restype = vp
+    lib.fake_get.restype, lib.fake_get.argtypes = ctypes.c_long, [ctypes.c_char_p]
+    lib.fake_set.argtypes = [ctypes.c_char_p, ctypes.c_long]
+    lib.fake_error.restype = ctypes.c_char_p
+    return lib
+
+
+V = 100  # stops: two 64-word units of the pool
+CALLER = vp(0x1000)  # a caller's stream
+
+
+def answer(s, ts):
+    return 1000 * s + ts
+
+
+class Fake:
+    def __init__(self, lib, slots, **ctl):
+        self.lib = lib
+        for k in ("hold", "finish", "fail_record", "fail_relax", "fail_copies", "attributes_us", "stream_device", "memcpys",
+                  "copy_launches", "overlaps", "stream_syncs", "attributes"):
+            lib.fake_set(k.encode(), ctl.get(k, 0))
+        g = (vp * 1)(lib.fake_graph(V))
+        o = SessionOptions(pool_bytes=slots * 128 * 4, n_streams=4)
+        self.h = vp()
+        assert lib.eat_session_create(g, 1, ctypes.byref(o), ctypes.byref(self.h)) == OK
+
+    def get(self, name):
+        return self.lib.fake_get(name.encode())
+
+    def admit(self, s, ts):
+        slot = i32()
+        st = self.lib.eat_session_admit(self.h, 0, s, ts, ctypes.byref(slot))
+        return slot.value if st == OK else None
+
+    def step(self):
+        assert self.lib.eat_session_step(self.h, None) == OK
+
+    def poll(self):
+        a, n = (i32 * 4096)(), i32()
+        assert self.lib.eat_session_poll(self.h, a, 4096, ctypes.byref(n)) == OK
+        return list(a[:n.value])
+
+    def result(self, slot):
+        p, n = ctypes.POINTER(i32)(), i32()
+        assert self.lib.eat_session_result(self.h, slot, ctypes.byref(p), ctypes.byref(n)) == OK
+        return list(p[:n.value])
+
+    def buffers(self, n):
+        return [self.lib.fake_alloc(V) for _ in range(n)]
+
+    def serve(self, n, dst=None, arrival=None, min_batch=1000):
+        """(status, latency, report); a guard word on each side of every array."""
+        def arr(x, dt):
+            a = np.full(n + 2, -77, dt)
+            a[1:n + 1] = x
+            return a
+        src, ts = arr(np.arange(n) % V, np.int32), arr(10 + np.arange(n), np.int32)
+        gr, at = arr(np.zeros(n), np.int32), arr(np.zeros(n) if arrival is None else arrival, np.float64)
+        lat, rep = arr(np.full(n, -5.0), np.float64), Report()
+        d = (vp * (n + 2))(*([None] + list(dst) + [None])) if dst is not None else None
+        at_ = lambda a: vp(a.ctypes.data + a.itemsize)  # noqa: E731
+        st = self.lib.eat_session_serve(self.h, n, at_(gr), at_(src), at_(ts), at_(at), min_batch,
+                                        ctypes.c_double(0.0), vp(ctypes.addressof(d) + 8) if d is not None else None,
+                                        CALLER, at_(lat), ctypes.byref(rep))
+        assert lat[0] == -77 and lat[-1] == -77
+        return st, lat[1:-1], rep
+
+    def room(self):
+        """Slots that can be admitted now (they are given back)."""
+        got = []
+        while (s := self.admit(0, 0)) is not None:
+            got.append(s)
+        for s in got:
+            assert self.lib.eat_session_release(self.h, s) == OK
+        return len(got)
+
+
+def holds(p, n, value):
+    a = ctypes.cast(p, ctypes.POINTER(i32))
+    return all(a[k] == value for k in range(n))
+
+
+def test_serve_answers_and_copies(lib):
+    f = Fake(lib, 300)
+    dst = f.buffers(200)
+    st, lat, rep = f.serve(200, dst)
+    assert st == OK and rep.launched == 200 and np.all(lat >= 0)
+    assert all(holds(d, V, answer(i % V, 10 + i)) for i, d in enumerate(dst))
+    assert f.room() == 300 and f.poll() == []
+
+
+def test_results_stay_listed_when_their_copies_fail(lib):
+    f = Fake(lib, 100, fail_copies=1)
+    st, lat, _ = f.serve(40, f.buffers(40))
+    assert st != OK and np.all(lat >= 0)
+    got = f.poll()
+    assert sorted(f.result(s)[0] for s in got) == sorted(answer(i, 10 + i) for i in range(40))
+    for s in got:
+        assert f.lib.eat_session_release(f.h, s) == OK
+    assert f.room() == 100
+
+
+def test_results_that_wait_for_a_copy_stay_listed_when_a_step_fails(lib):
+    # three bursts of 10, 5 of each finish: the first five are being copied, the second
+    # five wait for that copy, the third burst's step fails
+    f = Fake(lib, 100, hold=1, finish=5, fail_relax=3)
+    dst = f.buffers(30)
+    st, lat, _ = f.serve(30, dst, arrival=np.repeat([0, 0.01, 0.02], 10), min_batch=10)
+    assert st != OK
+    f.lib.fake_drain()
+    assert all(holds(d, V, answer(i, 10 + i)) for i, d in enumerate(dst[:5]))
+    assert sorted(f.result(s)[0] for s in f.poll()) == [answer(i, 10 + i) for i in range(10, 15)]

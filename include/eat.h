@@ -564,7 +564,11 @@ typedef struct {
  * requests are checked before the first one is admitted
  * (EAT_ERR_INVALID_ARGUMENT, also for a graph whose result slot is larger
  * than the whole pool); the session must hold no admitted or unfinished
- * query when called.  rep (nullable) receives the counts.  This is the
+ * query when called.  Finished slots of earlier queries stay as they are, and
+ * are polled and released by the caller; EAT_ERR_BUSY if they leave no room for
+ * a request.  When a call fails half way, its finished slots that have not been
+ * copied stay finished slots of the session.  rep (nullable) receives the
+ * counts.  This is the
  * request loop of a server, in native code: Section I's queries, answered by
  * eat_session_step launches. */
 eat_status eat_session_serve(eat_session *sess, int32_t n, const int32_t *graph, const int32_t *src,

@@ -633,7 +633,10 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
   // queries, 30 polls with results: the events alone kept the copy stream busy for
   // 0.2 ms after the last query); a full list, a request without a slot, or the end
   // of all launched queries does not let it wait.
-  size_t seen = 0;
+  // The first `others` of them are the caller's, finished before the call and not
+  // polled yet: they stay as they are.
+  const size_t others = S->finished.size();
+  size_t seen = others;
   std::vector<int32_t> group;
   CopyMark *last = nullptr;
   struct LastMark {  // the loop's own reference ends with it
@@ -653,6 +656,8 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
       int32_t slot = -1;
       const eat_status st = eat_session_admit(S, graph[r], src[r], ts[r], &slot);
       if (st == EAT_ERR_BUSY) {
+        if (unfinished == 0 && pending.empty() && S->finished.size() == others && S->deferred.empty())
+          return set_err(EAT_ERR_BUSY, "the session's finished slots leave no room for request " + std::to_string(r));
         ++busy;
         break;
       }
@@ -684,15 +689,15 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
         --unfinished;
       }
     }
-    if (seen > 0 &&
-        (unfinished == 0 || !waiting.empty() || seen >= (size_t)eat::kCopySlabs || !copy_dst || !last ||
+    if (seen > others &&
+        (unfinished == 0 || !waiting.empty() || seen - others >= (size_t)eat::kCopySlabs || !copy_dst || !last ||
          hipEventQuery(last->event) != hipErrorNotReady)) {
-      group.assign(S->finished.begin(), S->finished.end());
+      group.assign(S->finished.begin() + (std::ptrdiff_t)others, S->finished.end());
       st = copy_and_release(S, group.data(), (int32_t)group.size(), req_of.data(), copy_dst, copy_stream, local, &last);
       if (st != EAT_OK) return st;
       for (const int32_t slot : group) req_of[(size_t)slot] = -1;
       done += (int32_t)group.size();
-      seen = 0;
+      seen = others;
     } else if (unfinished == 0 && pending.empty() && waiting.empty() && next < n) {
       const double gap = arrival_s[next] - now_s();  // idle until the next arrival
       if (gap > 200e-6) std::this_thread::sleep_for(std::chrono::duration<double>(gap - 100e-6));

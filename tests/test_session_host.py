@@ -143,3 +143,34 @@ def test_results_that_wait_for_a_copy_stay_listed_when_a_step_fails(lib):
     f.lib.fake_drain()
     assert all(holds(d, V, answer(i, 10 + i)) for i, d in enumerate(dst[:5]))
     assert sorted(f.result(s)[0] for s in f.poll()) == [answer(i, 10 + i) for i in range(10, 15)]
+
+
+@pytest.mark.parametrize("own", [1, 3])
+@pytest.mark.parametrize("n", [1, 70])
+def test_finished_slots_of_the_caller_are_left_alone(lib, own, n):
+    f = Fake(lib, 100)
+    mine = [f.admit(90 + i, 5) for i in range(own)]
+    f.step()
+    assert f.lib.eat_session_sync(f.h) == OK
+    dst = f.buffers(n)
+    st, lat, rep = f.serve(n, dst)
+    assert st == OK and rep.launched == n and np.all(lat >= 0)
+    assert all(holds(d, V, answer(i, 10 + i)) for i, d in enumerate(dst))
+    assert f.poll() == mine  # finished, not polled yet: as before the call
+    assert [f.result(s)[0] for s in mine] == [answer(90 + i, 5) for i in range(own)]
+    assert f.room() == 100 - own
+
+
+@pytest.mark.parametrize("polled", [False, True])
+def test_requests_that_can_never_get_a_slot_are_refused(lib, polled):
+    f = Fake(lib, 3)
+    mine = [f.admit(90 + i, 5) for i in range(3)]  # all of the pool
+    f.step()
+    assert f.lib.eat_session_sync(f.h) == OK
+    if polled:
+        assert f.poll() == mine
+    st, lat, _ = f.serve(4, f.buffers(4))
+    assert st == BUSY
+    for s in mine:
+        assert f.lib.eat_session_release(f.h, s) == OK
+    assert f.serve(4, f.buffers(4))[0] == OK and f.room() == 3

@@ -484,7 +484,7 @@ extern "C" eat_status eat_session_copy(eat_session *S, int32_t slot, int32_t *ds
   eat_status st = eat_session_result(S, slot, &src, &n);
   if (st != EAT_OK) return st;
   if (!dst) return set_err(EAT_ERR_INVALID_ARGUMENT, "dst is NULL");
-  HIP_TRY(hipMemcpyAsync(dst, src, (size_t)n * 4, hipMemcpyDefault, static_cast<hipStream_t>(stream)));
+  hipStream_t hs = static_cast<hipStream_t>(stream);
   Slot &sl = S->slots[(size_t)slot];
   if (!sl.copy) {
     try {
@@ -494,7 +494,12 @@ extern "C" eat_status eat_session_copy(eat_session *S, int32_t slot, int32_t *ds
     if (!sl.copy) return set_err(EAT_ERR_DEVICE, "copy event");
     sl.copy->refs = 1;
   }
-  HIP_TRY(hipEventRecord(sl.copy->event, static_cast<hipStream_t>(stream)));
+  HIP_TRY(hipMemcpyAsync(dst, src, (size_t)n * 4, hipMemcpyDefault, hs));
+  const hipError_t e = hipEventRecord(sl.copy->event, hs);
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(hs);  // nothing else tells when the slab has been read
+    return hip_err(e, "result copy");
+  }
   return EAT_OK;
 }
 
@@ -543,46 +548,55 @@ extern "C" void eat_session_free(eat_session *S) { destroy(S); }
 // released.
 // ---------------------------------------------------------------------------
 // Copies and releases finished slots: the copies to memory of this device in one
-// launch per kCopySlabs of them, with one event at their end (*last: its mark,
-// one reference of the caller's), any other copy by itself.
+// launch per kCopySlabs of them, each with an event behind it (*last: the last
+// one's mark, one reference of the caller's), any other copy by itself.  A slot is
+// released when its copy has its event; the others stay as they are if a call
+// fails.
 static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t n, const int32_t *req_of,
                                    int32_t *const *copy_dst, void *stream, const std::vector<char> &local,
                                    CopyMark **last) {
   hipStream_t hs = static_cast<hipStream_t>(stream);
   eat::CopyList list{};
-  CopyMark *mark = nullptr;
+  int32_t to_copy[eat::kCopySlabs];  // the list's slots
+  auto launch = [&]() -> eat_status {
+    if (list.n == 0) return EAT_OK;
+    CopyMark *mark = new_mark(S);
+    if (!mark) return set_err(EAT_ERR_DEVICE, "copy event");
+    ++mark->refs;  // this function's
+    hipError_t e = eat::launch_copy_slabs(list, hs);
+    if (e == hipSuccess && (e = hipEventRecord(mark->event, hs)) != hipSuccess)
+      (void)hipStreamSynchronize(hs);  // nothing else tells when the slabs have been read
+    if (e != hipSuccess) {
+      drop_mark(S, mark);
+      return hip_err(e, "result copies");
+    }
+    if (*last) drop_mark(S, *last);
+    *last = mark;  // ... is now the caller's
+    for (int32_t j = 0; j < list.n; ++j) S->slots[(size_t)to_copy[j]].copy = mark;
+    mark->refs += list.n;
+    for (int32_t j = 0; j < list.n; ++j) {
+      const eat_status st = release_slot(S, to_copy[j], true);
+      if (st != EAT_OK) return st;
+    }
+    list.n = 0;
+    return EAT_OK;
+  };
   for (int32_t j = 0; j < n; ++j) {
     const int32_t r = req_of[slots[j]];
-    if (!copy_dst || !copy_dst[r]) continue;
-    Slot &sl = S->slots[(size_t)slots[j]];
-    if (!local[(size_t)r]) {
-      const eat_status st = eat_session_copy(S, slots[j], copy_dst[r], stream);
-      if (st != EAT_OK) return st;
-      continue;
+    int32_t *dst = copy_dst ? copy_dst[r] : nullptr;
+    eat_status st = EAT_OK;
+    if (dst && local[(size_t)r]) {
+      const Slot &sl = S->slots[(size_t)slots[j]];
+      to_copy[list.n] = slots[j];
+      list.e[list.n++] = eat::SlabCopy{S->d_pool + sl.off, dst, S->graphs[(size_t)sl.graph]->info.n_vertices};
+      if (list.n == eat::kCopySlabs) st = launch();
+    } else {
+      if (dst) st = eat_session_copy(S, slots[j], dst, stream);
+      if (st == EAT_OK) st = release_slot(S, slots[j], false);
     }
-    if (!mark && !(mark = new_mark(S))) return set_err(EAT_ERR_DEVICE, "copy event");
-    list.e[list.n++] = eat::SlabCopy{S->d_pool + sl.off, copy_dst[r], S->graphs[(size_t)sl.graph]->info.n_vertices};
-    sl.copy = mark;
-    ++mark->refs;
-    if (list.n == eat::kCopySlabs) {
-      const hipError_t e = eat::launch_copy_slabs(list, hs);
-      if (e != hipSuccess) return hip_err(e, "result copies");
-      list.n = 0;
-    }
-  }
-  if (mark) {
-    const hipError_t e = eat::launch_copy_slabs(list, hs);
-    if (e != hipSuccess) return hip_err(e, "result copies");
-    HIP_TRY(hipEventRecord(mark->event, hs));
-    if (*last) drop_mark(S, *last);
-    ++mark->refs;
-    *last = mark;
-  }
-  for (int32_t j = 0; j < n; ++j) {
-    const eat_status st = release_slot(S, slots[j], mark && S->slots[(size_t)slots[j]].copy == mark);
     if (st != EAT_OK) return st;
   }
-  return EAT_OK;
+  return launch();
 }
 
 static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, const int32_t *src,

@@ -149,8 +149,8 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t st) {
 hipError_t hipEventQuery(hipEvent_t e) {
   return reinterpret_cast<Event *>(e)->pending ? hipErrorNotReady : hipSuccess;
 }
-hipError_t hipEventSynchronize(hipEvent_t) {
-  drain();
+hipError_t hipEventSynchronize(hipEvent_t e) {
+  if (reinterpret_cast<Event *>(e)->pending) drain();
   return hipSuccess;
 }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {

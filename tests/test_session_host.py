@@ -174,3 +174,26 @@ def test_requests_that_can_never_get_a_slot_are_refused(lib, polled):
     for s in mine:
         assert f.lib.eat_session_release(f.h, s) == OK
     assert f.serve(4, f.buffers(4))[0] == OK and f.room() == 3
+
+
+# the first copy launch of 64 results is under way when the next one, or the event
+# behind one, fails: no slab may be given out while it is still being copied
+@pytest.mark.parametrize("n,ctl", [(100, {"fail_copies": 2}), (150, {"fail_copies": 3}), (40, {"fail_record": 1}),
+                                   (100, {"fail_record": 1}), (100, {"fail_record": 2})], ids=str)
+def test_slabs_under_copy_are_kept_when_a_copy_fails(lib, n, ctl):
+    f = Fake(lib, 200, hold=1, **ctl)
+    dst = f.buffers(n)
+    assert f.serve(n, dst)[0] != OK
+    for s in f.poll():
+        assert f.lib.eat_session_release(f.h, s) == OK
+    taken = 0
+    while f.admit(99, 7) is not None:  # take all that is free, and overwrite it
+        taken += 1
+        f.step()
+        assert f.lib.eat_session_sync(f.h) == OK
+    launched = f.get("copy_launches") - (1 if "fail_copies" in ctl else 0)
+    assert taken == 200 - 64 * launched or f.get("stream_syncs") > 0  # kept, or waited for
+    f.lib.fake_drain()
+    for i, d in enumerate(dst[:64 * launched]):
+        assert holds(d, V, answer(i % V, 10 + i)), i
+    assert not any(holds(d, V, answer(99, 7)) for d in dst)

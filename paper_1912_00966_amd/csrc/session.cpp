@@ -587,8 +587,15 @@ static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t
     eat_status st = EAT_OK;
     if (dst && local[(size_t)r]) {
       const Slot &sl = S->slots[(size_t)slots[j]];
+      const int32_t words = S->graphs[(size_t)sl.graph]->info.n_vertices;
+      // a launch writes its slabs side by side: one that overlaps another follows it
+      bool meets = false;
+      for (int32_t k = 0; k < list.n; ++k)
+        meets |= dst < list.e[k].dst + list.e[k].words && list.e[k].dst < dst + words;
+      if (meets) st = launch();
+      if (st != EAT_OK) return st;
       to_copy[list.n] = slots[j];
-      list.e[list.n++] = eat::SlabCopy{S->d_pool + sl.off, dst, S->graphs[(size_t)sl.graph]->info.n_vertices};
+      list.e[list.n++] = eat::SlabCopy{S->d_pool + sl.off, dst, words};
       if (list.n == eat::kCopySlabs) st = launch();
     } else {
       if (dst) st = eat_session_copy(S, slots[j], dst, stream);

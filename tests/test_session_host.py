@@ -197,3 +197,23 @@ def test_slabs_under_copy_are_kept_when_a_copy_fails(lib, n, ctl):
     for i, d in enumerate(dst[:64 * launched]):
         assert holds(d, V, answer(i % V, 10 + i)), i
     assert not any(holds(d, V, answer(99, 7)) for d in dst)
+
+
+# requests with one destination, or with destinations that overlap in part: copies one
+# after the other, the one that finished last on top
+@pytest.mark.parametrize("shift", [0, 1, V - 1])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 130])
+def test_destinations_that_overlap_are_written_one_after_the_other(lib, n, shift):
+    f = Fake(lib, 200)
+    room = f.lib.fake_alloc(V + n * shift)
+    st, _, _ = f.serve(n, [room + 4 * shift * i for i in range(n)])
+    assert st == OK and f.get("overlaps") == 0
+    a = ctypes.cast(room, ctypes.POINTER(i32))
+    assert holds(room + 4 * shift * (n - 1), V, answer((n - 1) % V, 9 + n))
+    if shift > 0:
+        assert all(a[shift * i] == answer(i % V, 10 + i) for i in range(n))
+    # destinations side by side still share launches
+    f.lib.fake_set(b"copy_launches", 0)
+    room = f.lib.fake_alloc(V * n)
+    assert f.serve(n, [room + 4 * V * i for i in range(n)])[0] == OK
+    assert f.get("copy_launches") == (n + 63) // 64 and f.get("overlaps") == 0

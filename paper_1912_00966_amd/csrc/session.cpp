@@ -547,14 +547,21 @@ extern "C" void eat_session_free(eat_session *S) { destroy(S); }
 // admission, steps by the batching policy, completions polled, copied and
 // released.
 // ---------------------------------------------------------------------------
+// True for memory of the session's device.
+static bool on_device(const eat_session *S, const int32_t *p) {
+  hipPointerAttribute_t at{};
+  if (hipPointerGetAttributes(&at, p) == hipSuccess) return at.type == hipMemoryTypeDevice && at.device == S->device;
+  (void)hipGetLastError();  // ordinary host memory
+  return false;
+}
+
 // Copies and releases finished slots: the copies to memory of this device in one
 // launch per kCopySlabs of them, each with an event behind it (*last: the last
 // one's mark, one reference of the caller's), any other copy by itself.  A slot is
 // released when its copy has its event; the others stay as they are if a call
 // fails.
 static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t n, const int32_t *req_of,
-                                   int32_t *const *copy_dst, void *stream, const std::vector<char> &local,
-                                   CopyMark **last) {
+                                   int32_t *const *copy_dst, void *stream, CopyMark **last) {
   hipStream_t hs = static_cast<hipStream_t>(stream);
   eat::CopyList list{};
   int32_t to_copy[eat::kCopySlabs];  // the list's slots
@@ -585,7 +592,7 @@ static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t
     const int32_t r = req_of[slots[j]];
     int32_t *dst = copy_dst ? copy_dst[r] : nullptr;
     eat_status st = EAT_OK;
-    if (dst && local[(size_t)r]) {
+    if (dst && on_device(S, dst)) {
       const Slot &sl = S->slots[(size_t)slots[j]];
       const int32_t words = S->graphs[(size_t)sl.graph]->info.n_vertices;
       // a launch writes its slabs side by side: one that overlaps another follows it
@@ -630,17 +637,6 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
     if (!(arrival_s[i] >= 0.0) || (i > 0 && arrival_s[i] < arrival_s[i - 1]))
       return set_err(EAT_ERR_INVALID_ARGUMENT, "arrival_s must be >= 0 and non-decreasing");
   }
-  // which results go to memory of this device
-  std::vector<char> local((size_t)n, 0);
-  if (copy_dst)
-    for (int32_t i = 0; i < n; ++i) {
-      if (!copy_dst[i]) continue;
-      hipPointerAttribute_t at{};
-      if (hipPointerGetAttributes(&at, copy_dst[i]) == hipSuccess)
-        local[(size_t)i] = at.type == hipMemoryTypeDevice && at.device == S->device;
-      else
-        (void)hipGetLastError();  // ordinary host memory
-    }
   using Clock = std::chrono::steady_clock;
   const Clock::time_point t0 = Clock::now();
   auto now_s = [&]() { return std::chrono::duration<double>(Clock::now() - t0).count(); };
@@ -714,7 +710,7 @@ static eat_status serve_loop(eat_session *S, int32_t n, const int32_t *graph, co
         (unfinished == 0 || !waiting.empty() || seen - others >= (size_t)eat::kCopySlabs || !copy_dst || !last ||
          hipEventQuery(last->event) != hipErrorNotReady)) {
       group.assign(S->finished.begin() + (std::ptrdiff_t)others, S->finished.end());
-      st = copy_and_release(S, group.data(), (int32_t)group.size(), req_of.data(), copy_dst, copy_stream, local, &last);
+      st = copy_and_release(S, group.data(), (int32_t)group.size(), req_of.data(), copy_dst, copy_stream, &last);
       if (st != EAT_OK) return st;
       for (const int32_t slot : group) req_of[(size_t)slot] = -1;
       done += (int32_t)group.size();

@@ -217,3 +217,19 @@ def test_destinations_that_overlap_are_written_one_after_the_other(lib, n, shift
     room = f.lib.fake_alloc(V * n)
     assert f.serve(n, [room + 4 * V * i for i in range(n)])[0] == OK
     assert f.get("copy_launches") == (n + 63) // 64 and f.get("overlaps") == 0
+
+
+def test_the_time_of_a_call_counts_from_its_start(lib):
+    n = 50
+    f = Fake(lib, 100, attributes_us=2000)
+    st, lat, rep = f.serve(n, f.buffers(n))
+    assert st == OK and f.get("attributes") == n  # the destinations are looked at once
+    assert rep.wall_s >= n * 2e-3  # "from the call until the last query finished"
+
+
+def test_requests_do_not_queue_up_while_destinations_are_looked_at(lib):
+    # 200 destinations of 1 ms each; the first request has its answer before that
+    n = 200
+    f = Fake(lib, 300, attributes_us=1000)
+    st, lat, _ = f.serve(n, f.buffers(n), arrival=np.concatenate([[0], np.full(n - 1, 0.02)]), min_batch=1)
+    assert st == OK and lat[0] < 0.02

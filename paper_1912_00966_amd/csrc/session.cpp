@@ -563,6 +563,9 @@ static bool on_device(const eat_session *S, const int32_t *p) {
 static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t n, const int32_t *req_of,
                                    int32_t *const *copy_dst, void *stream, CopyMark **last) {
   hipStream_t hs = static_cast<hipStream_t>(stream);
+  // a stream of another device takes copies, but no kernel of this one
+  hipDevice_t dev = S->device;
+  const bool stream_here = !hs || (hipStreamGetDevice(hs, &dev) == hipSuccess && dev == S->device);
   eat::CopyList list{};
   int32_t to_copy[eat::kCopySlabs];  // the list's slots
   auto launch = [&]() -> eat_status {
@@ -592,7 +595,7 @@ static eat_status copy_and_release(eat_session *S, const int32_t *slots, int32_t
     const int32_t r = req_of[slots[j]];
     int32_t *dst = copy_dst ? copy_dst[r] : nullptr;
     eat_status st = EAT_OK;
-    if (dst && on_device(S, dst)) {
+    if (dst && stream_here && on_device(S, dst)) {
       const Slot &sl = S->slots[(size_t)slots[j]];
       const int32_t words = S->graphs[(size_t)sl.graph]->info.n_vertices;
       // a launch writes its slabs side by side: one that overlaps another follows it

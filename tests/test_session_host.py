@@ -233,3 +233,11 @@ def test_requests_do_not_queue_up_while_destinations_are_looked_at(lib):
     f = Fake(lib, 300, attributes_us=1000)
     st, lat, _ = f.serve(n, f.buffers(n), arrival=np.concatenate([[0], np.full(n - 1, 0.02)]), min_batch=1)
     assert st == OK and lat[0] < 0.02
+
+
+def test_a_copy_stream_of_another_device_gets_plain_copies(lib):
+    f = Fake(lib, 100, stream_device=1)
+    dst = f.buffers(70)
+    assert f.serve(70, dst)[0] == OK
+    assert f.get("copy_launches") == 0 and f.get("memcpys") == 70  # a kernel cannot be launched there
+    assert all(holds(d, V, answer(i % V, 10 + i)) for i, d in enumerate(dst))

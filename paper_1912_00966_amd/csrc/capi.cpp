@@ -813,14 +813,9 @@ eat_status eat::plan_batch(const eat_graph *const *graphs, int32_t n_graphs, con
   return EAT_OK;
 }
 
-static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph,
-                               const int32_t *q_src, const int32_t *q_ts, const int32_t *q_dst, int32_t n_q,
-                               int32_t *const *arr, const eat_run_options *ro, eat_batch **out) {
-  if (!out) return set_err(EAT_ERR_INVALID_ARGUMENT, "out is NULL");
-  *out = nullptr;
-  eat::BatchPlan bp;
-  const eat_status st = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, q_dst, n_q, arr, ro, &bp);
-  if (st != EAT_OK) return st;
+eat_status eat::batch_from_plan(const BatchPlan &bp, const eat_graph *const *graphs, int32_t n_graphs,
+                                const int32_t *q_dst, eat_batch **out) {
+  const int32_t n_q = (int32_t)bp.qs.size();
   const std::vector<QueryDev> &qs = bp.qs;
   const std::vector<int32_t> &boff = bp.boff;
   const Plan &pl = bp.pl;
@@ -888,6 +883,16 @@ static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs,
   a.targets = d_t;
   *out = b;
   return EAT_OK;
+}
+
+static eat_status batch_create(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph,
+                               const int32_t *q_src, const int32_t *q_ts, const int32_t *q_dst, int32_t n_q,
+                               int32_t *const *arr, const eat_run_options *ro, eat_batch **out) {
+  if (!out) return set_err(EAT_ERR_INVALID_ARGUMENT, "out is NULL");
+  *out = nullptr;
+  eat::BatchPlan bp;
+  const eat_status st = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, q_dst, n_q, arr, ro, &bp);
+  return st == EAT_OK ? eat::batch_from_plan(bp, graphs, n_graphs, q_dst, out) : st;
 }
 
 extern "C" eat_status eat_batch_create(const eat_graph *const *graphs, int32_t n_graphs,
@@ -1006,38 +1011,36 @@ extern "C" eat_status eat_query_batch(const eat_graph *const *graphs, int32_t n_
                                       const int32_t *q_ts, int32_t n_q, int32_t *const *arr,
                                       void *stream, const eat_run_options *ro,
                                       eat_query_stats *stats) {
-  // A batch without statistics that fits the first graph's scratch allocates
-  // nothing: one upload, one launch, one wait (allocations, five blocking copies,
-  // an event and two frees were 0.13 ms of a 0.29 ms call of 100 queries).
-  if (graphs && n_graphs >= 1 && graphs[0] && n_q > 0 && n_q <= eat::kScratchQueries && !stats) {
-    eat::ScratchLock lock(graphs[0]);
-    if (eat::CallScratch *sc = lock.get()) {
-      try {
-        eat::BatchPlan bp;
-        const eat_status st = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, nullptr, n_q, arr, ro, &bp);
-        if (st != EAT_OK) return st;
-        if (eat::fits_scratch(bp, n_graphs)) {
-          hipStream_t hs = static_cast<hipStream_t>(stream);
-          const hipError_t e = eat::launch_from_scratch(bp, graphs, n_graphs, sc, hs);
-          const hipError_t w = eat::wait_scratch(sc, hs);
-          if (e != hipSuccess) return hip_err(e, "relaxation launch");
-          if (w != hipSuccess) return hip_err(w, "batch completion");
-          return eat::batch_status(sc->out[0]);
-        }
-      } catch (const std::bad_alloc &) {  // nothing throws across the C ABI
-        return set_err(EAT_ERR_OUT_OF_MEMORY, "host allocation failed");
+  try {
+    eat::BatchPlan bp;
+    eat_status s = eat::plan_batch(graphs, n_graphs, q_graph, q_src, q_ts, nullptr, n_q, arr, ro, &bp);
+    if (s != EAT_OK) return s;
+    // A batch without statistics that fits the first graph's scratch allocates
+    // nothing: one upload, one launch, one wait (allocations, five blocking copies,
+    // an event and two frees were 0.13 ms of a 0.29 ms call of 100 queries).
+    if (n_q > 0 && !stats && eat::fits_scratch(bp, n_graphs)) {
+      eat::ScratchLock lock(graphs[0]);
+      if (eat::CallScratch *sc = lock.get()) {
+        hipStream_t hs = static_cast<hipStream_t>(stream);
+        const hipError_t e = eat::launch_from_scratch(bp, graphs, n_graphs, sc, hs);
+        const hipError_t w = eat::wait_scratch(sc, hs);
+        if (e != hipSuccess) return hip_err(e, "relaxation launch");
+        if (w != hipSuccess) return hip_err(w, "batch completion");
+        return eat::batch_status(sc->out[0]);
       }
     }
+    eat_batch *b = nullptr;
+    s = eat::batch_from_plan(bp, graphs, n_graphs, nullptr, &b);
+    if (s != EAT_OK) return s;
+    s = eat_batch_run(b, stream);
+    if (s == EAT_OK) s = eat_batch_wait(b, stats);
+    std::string keep = g_last_error;
+    eat_batch_free(b);
+    g_last_error = keep;
+    return s;
+  } catch (const std::bad_alloc &) {  // nothing throws across the C ABI
+    return set_err(EAT_ERR_OUT_OF_MEMORY, "host allocation failed");
   }
-  eat_batch *b = nullptr;
-  eat_status s = eat_batch_create(graphs, n_graphs, q_graph, q_src, q_ts, n_q, arr, ro, &b);
-  if (s != EAT_OK) return s;
-  s = eat_batch_run(b, stream);
-  if (s == EAT_OK) s = eat_batch_wait(b, stats);
-  std::string keep = g_last_error;
-  eat_batch_free(b);
-  g_last_error = keep;
-  return s;
 }
 
 // ---------------------------------------------------------------------------

@@ -116,7 +116,8 @@ eat_status make_plan(const eat_run_options *ro, int32_t max_v, int device, Plan 
 // and free.
 class ScratchLock {
  public:
-  explicit ScratchLock(const eat_graph *g) {
+  explicit ScratchLock(const eat_graph *g) {  // nullptr: none
+    if (!g) return;
     CallScratch &s = const_cast<eat_graph *>(g)->scratch;
     if (s.dev && s.mu.try_lock()) s_ = &s;
   }
@@ -145,6 +146,9 @@ struct BatchPlan {
 eat_status plan_batch(const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_graph, const int32_t *q_src,
                       const int32_t *q_ts, const int32_t *q_dst, int32_t n_q, int32_t *const *arr,
                       const eat_run_options *ro, BatchPlan *out);
+// The batch of a plan (q_dst: the plan's destinations).  May throw std::bad_alloc.
+eat_status batch_from_plan(const BatchPlan &bp, const eat_graph *const *graphs, int32_t n_graphs, const int32_t *q_dst,
+                           eat_batch **out);
 // True if a planned batch of n_graphs graphs fits a graph's scratch.
 bool fits_scratch(const BatchPlan &bp, int32_t n_graphs);
 // Enqueues a planned batch on the stream from a graph's scratch: one upload, one

@@ -89,7 +89,8 @@ typedef struct {
   int64_t n_ap_clusters;     /* ... stored as one progression */
   int64_t n_array_clusters;  /* ... stored as a sorted array */
   int64_t n_pool;            /* int32 words of the departure pool */
-  int64_t device_bytes;      /* device memory held by the graph */
+  int64_t device_bytes;      /* device memory held by the graph: its arrays, and from the
+                                first one-shot batch or profile on their scratch */
   int64_t n_grid_entries;    /* header-grid entries on the device (0: no grid) */
   int64_t n_trips;           /* *_build_trips: vehicle trips in the input */
   int64_t n_shortcuts;       /* *_build_trips: sub-trip shortcut connections added

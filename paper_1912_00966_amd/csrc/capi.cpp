@@ -275,9 +275,19 @@ void make_scratch(eat_graph *g) {
   s.row = reinterpret_cast<int32_t *>(s.dev + up);
   s.out = reinterpret_cast<int32_t *>(s.host + up);
   s.out_dev = reinterpret_cast<int32_t *>(static_cast<char *>(hd) + up);
+  s.device_bytes = (int64_t)(up + row);
 }
 
 }  // namespace
+
+eat::ScratchLock::ScratchLock(const eat_graph *g) {
+  if (!g) return;
+  CallScratch &s = const_cast<eat_graph *>(g)->scratch;
+  if (!s.mu.try_lock()) return;
+  if (!s.dev) make_scratch(const_cast<eat_graph *>(g));
+  if (s.dev) s_ = &s;
+  else s.mu.unlock();
+}
 
 extern "C" eat_status eat_graph_upload(const eat_layout *L, const eat_build_options *opt, void *stream,
                                        eat_graph **out) {
@@ -404,7 +414,6 @@ extern "C" eat_status eat_graph_upload(const eat_layout *L, const eat_build_opti
     delete g;
     return hip_err(ue, "graph upload");
   }
-  make_scratch(g);
   *out = g;
   return EAT_OK;
 }
@@ -451,6 +460,7 @@ extern "C" void eat_graph_free(eat_graph *g) {
 extern "C" eat_status eat_graph_info(const eat_graph *g, eat_graph_info_t *out) {
   if (!g || !out) return set_err(EAT_ERR_INVALID_ARGUMENT, "NULL argument");
   *out = g->info;
+  out->device_bytes += g->scratch.device_bytes;
   return EAT_OK;
 }
 

@@ -1,6 +1,7 @@
 """One-shot batches and profiles that a graph's scratch does not take in part or at
 all, bit-exact against the CPU oracle: more departures than it holds, and graphs
 whose activity bitmap is in HBM."""
+import ctypes
 import functools
 
 import numpy as np
@@ -73,3 +74,27 @@ def test_graphs_whose_bitmap_is_in_hbm():
     dep, arr = g.profile(5, 0, 86_400)
     e_dep, e_arr = csa.profile(5, 0, 86_400)
     assert np.array_equal(dep, e_dep) and np.array_equal(arr.cpu().numpy(), e_arr)
+
+
+def _device_bytes(g):
+    gi = eat.GraphInfo()
+    assert eat.lib().eat_graph_info(g.handle, ctypes.byref(gi)) == 0
+    return gi.device_bytes
+
+
+@pytest.mark.parametrize("first", ["batch", "profile"])
+def test_the_scratch_is_made_by_the_first_call_and_counted(first):
+    n = 500_000
+    u, t = np.arange(4, dtype=np.int32), np.full(4, 50, np.int32)
+    g = eat.eat_graph_build(u, u + 1, t, t, n)
+    out = torch.empty((1, n), dtype=torch.int32, device="cuda")
+    held = _device_bytes(g)
+    assert 8 * n <= held < 10 * n  # the stops' type ranges: no result row
+    g.query(0, 0, out=out[0])
+    assert _device_bytes(g) == held
+    for _ in range(2):
+        if first == "batch":
+            eat.eat_query_batch([g], np.zeros(1, np.int32), np.zeros(1, np.int32), np.zeros(1, np.int32), [out[0]])
+        else:
+            g.profile(0, 0, 100)
+        assert held + 4 * n <= _device_bytes(g) < held + 5 * n

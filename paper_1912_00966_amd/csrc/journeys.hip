@@ -90,7 +90,7 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t x) {
 // chunks of kDepSpan seconds and sets a bit per departure in LDS; the bits'
 // prefix sum gives each departure its place.  out[0..cap) receives the first cap
 // of them; info[0] = their count, info[1] = the first departure after hi (INF if
-// none); out and info are host memory.
+// none); out and info are host memory (a graph's scratch) or device memory.
 //
 // What bounds it is the longest chain of one type's departures, one read each (a
 // wave that took the minimum over the types for every departure in turn made 32

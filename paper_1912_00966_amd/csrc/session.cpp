@@ -15,7 +15,8 @@
 // Result copies: eat_session_copy records an event on the caller's stream; a
 // slot released before that event has passed keeps its slab range out of the
 // pool until it has, so no later query overwrites a slab still being copied.
-// The request loop copies all results of a poll in one launch, with one event.
+// The request loop copies up to 64 finished results in one launch, with one event
+// behind it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

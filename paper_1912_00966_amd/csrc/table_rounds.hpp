@@ -23,7 +23,8 @@
 //   * Arrivals past the arrival window go to a far list.  It is read only when
 //     its earliest arrival has come inside the window, by the waves that have
 //     the fewest windows, while the others relax; what it promotes is expanded
-//     a round later.
+//     a round later.  So a query can take more rounds than with run_rounds, and
+//     one that hits its limit of rounds runs again with those.
 // Measured against the rounds with a take pass (relax.hpp's run_rounds, which
 // the slab store, virtual warps and two or three types per lane still use): a
 // query of 19 rounds alone on its CU 34 us instead of 54 (city of 50,000 stops),
